@@ -142,7 +142,7 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 // branch), else a generic split with up to 8 branches per lane over 1 or 2 lanes.  KC = 2 or 4: 16 bytes of compartments per lane
 // (BL KC = 4 for fp32, 8 for bf16) when the branch count allows, else one lane
 // holds the whole neuron (B KC <= 14).
-bool choose_mapping(int B, int KC, int io, bool bwd, int* BL, int* L, int* fast) {
+bool choose_mapping(int B, int KC, int io, bool bwd, bool longer, int* BL, int* L, int* fast) {
   if (KC == 1) {
     // The fp32 forward of 16 branches: 8 per lane over two lanes (the same
     // balanced branch-sum tree as the backward's 4 over four).  Measured on
@@ -154,7 +154,7 @@ bool choose_mapping(int B, int KC, int io, bool bwd, int* BL, int* L, int* fast)
       *BL = 8; *L = 2; *fast = 1;
       return true;
     }
-    const int blv = (io == DENDSN_IO_BF16 && B % 8 == 0 && !(bwd && B > 8 && B <= 64)) ? 8 : 4;
+    const int blv = (io == DENDSN_IO_BF16 && B % 8 == 0 && !(bwd && (B > 8 || longer) && B <= 64)) ? 8 : 4;
     if (B % blv == 0 && is_pow2(B / blv) && B / blv <= 16) {
       *BL = blv; *L = B / blv; *fast = 1;
       return true;
@@ -244,8 +244,8 @@ dendsn_status check_cfg(const dendsn_cfg* c) {
   if (channel_major(c)) {
     if (!cm_mapping(c->B, c->comps_per_branch, &BL, &L))
       return fail(DENDSN_E_UNSUPPORTED, "branch count not covered by the compiled channel-major kernels");
-  } else if (!choose_mapping(c->B, c->comps_per_branch, c->io, false, &BL, &L, &fast) ||
-             !choose_mapping(c->B, c->comps_per_branch, c->io, true, &BL, &L, &fast)) {
+  } else if (!choose_mapping(c->B, c->comps_per_branch, c->io, false, false, &BL, &L, &fast) ||
+             !choose_mapping(c->B, c->comps_per_branch, c->io, true, false, &BL, &L, &fast)) {
     return fail(DENDSN_E_UNSUPPORTED, "branch count not covered by the compiled kernels");
   }
   return DENDSN_OK;
@@ -258,6 +258,7 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   Plan p;
   memset(&p, 0, sizeof(p));
   p.KC = c->comps_per_branch;
+  const int64_t Ke = c->ckpt_every < c->T ? c->ckpt_every : c->T;  // steps of a whole segment
   if (channel_major(c)) {
     p.cm = 1; p.fast = 0;
     cm_mapping(c->B, c->comps_per_branch, &p.BL, &p.L);
@@ -266,7 +267,7 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
     // 523 -> 408 us with one lane and two positions per lane)
     if (!bwd && is_pow2(p.BL) && p.L >= 2 && p.BL * p.KC <= 4) { p.BL *= 2; p.L /= 2; }
   } else {
-    choose_mapping(c->B, c->comps_per_branch, c->io, bwd, &p.BL, &p.L, &p.fast);
+    choose_mapping(c->B, c->comps_per_branch, c->io, bwd, Ke > 4, &p.BL, &p.L, &p.fast);
   }
   const int L = p.L;
   const int esz = c->io == DENDSN_IO_BF16 ? 2 : 4;
@@ -342,9 +343,9 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   if (c->batch_groups > 0) G = c->batch_groups < c->batch ? c->batch_groups : c->batch;
   p.bpg = int32_t(ceil_div(c->batch, G));
   p.G = int32_t(ceil_div(c->batch, p.bpg));
-  const int64_t Ke = c->ckpt_every < c->T ? c->ckpt_every : c->T;
   p.nck = int32_t(ceil_div(c->T, c->ckpt_every) - 1);
-  p.KS = (p.fast && p.KC == 1 && !p.cm && p.BL <= 4 && Ke >= 8) ? 8 : 4;
+  const int E = p.BL * p.KC;
+  p.KS = (Ke > 4 && long_stash(p.BL, p.L, p.KC, p.cm)) ? 8 : 4;
   // Occupancy cap (measured on MI355X): the backward over conv-shaped tiles whose
   // lanes move 16 bytes per row runs 3-4 % faster with at most two blocks per CU
   // (fewer concurrent streams contending for DRAM pages), and with two positions
@@ -356,8 +357,23 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // lane) already hold about 70 KB of static LDS per block in the backward (the
   // DMA areas of their segment pipeline), which keeps them at two blocks per CU.
   const bool wide_sf = !p.cm && c->stateful && esz == 4 && p.BL * p.KC * esz > 16;
-  const bool cap = bwd && p.mode == kSpatial && p.BL * p.KC * esz >= 16 && (p.nw == 1 || p.L >= 2) && !wide_sf;
+  const bool cap = bwd && p.mode == kSpatial && p.BL * p.KC * esz >= 16 && (p.nw == 1 || p.L >= 2) && !wide_sf &&
+                   (p.KS == 4 || p.L >= 2);
   p.lds = cap ? int32_t(163840 / 3 + 256) : 0;
+  if (bwd) {
+    // Chunk-start slots of segments longer than KS: (E + 1) floats a lane and
+    // slot (the Stateless Dendrite: H alone), for the chunks between the first
+    // and the last.  At most 40 KB a block, then every second, fourth, ... start
+    // is kept.  The wide stateful fp32 lanes have no room beside their DMA area:
+    // up to kDmaChunks chunks keep none (short segments: advancing again from
+    // the segment's start costs little), more keep up to four in the area.
+    const int64_t slot = int64_t((c->stateful ? E : 0) + 1) * kThreads * 4;
+    const int64_t nch = ceil_div(Ke, p.KS);
+    const int64_t most = wide_sf ? (nch <= kDmaChunks ? 0 : 4) : 40960 / slot;
+    const int64_t n = nch > 2 ? nch - 2 : 0;
+    while ((n >> p.bsh) > most) ++p.bsh;
+    if (!wide_sf && (n >> p.bsh) * slot > p.lds) p.lds = int32_t((n >> p.bsh) * slot);
+  }
   // XCD runs (blocks are dealt to the 8 XCDs round-robin; measured on MI355X):
   // fully connected tiles in runs of 32 blocks per XCD (dbg forward / backward
   // -6 / -5 %, long horizon -5 / -3 %: neighbouring tiles share the cache lines
@@ -417,6 +433,7 @@ void fill_scan(const dendsn_cfg* c, const Plan& p, const void* x, const float* a
   s->beta = c->beta; s->vth = c->v_th;
   s->mode = p.mode; s->ways = p.ways; s->pb = p.pb; s->tpc = p.tpc; s->cpt = p.cpt; s->nw = p.nw;
   s->xk = p.xk;
+  s->bsh = p.bsh;
   s->stg = !p.cm && (s->M * s->P * (c->io == DENDSN_IO_BF16 ? 2 : 4)) % 16 == 0;
   s->bpg = p.bpg; s->ntiles = p.ntiles;
 }

@@ -14,28 +14,26 @@ namespace dendsn {
 constexpr int kVS = DENDSN_SG << 5;  // surrogate bit of the variant
 
 template <int BL, int L, int KS>
-static hipError_t launch_bwd_v(const dim3& grid, const BwdArgs& ba, int v, size_t lds, hipStream_t stream) {
+static hipError_t launch_bwd_v(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
   switch (v & 7) {
 #define DENDSN_V(n) \
-    case n: dendsn_bwd_kernel<bf16_t, BL, L, kVS | variant_bits(n), KS><<<grid, dim3(kThreads), lds, stream>>>(ba); break;
+    case n: return launch_bwd<bf16_t, BL, L, kVS | variant_bits(n), KS>(pl, ba, stream);
     DENDSN_EACH_VARIANT(DENDSN_V)
 #undef DENDSN_V
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 hipError_t DENDSN_SG_NAME(launch_bwd_bf16)(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned>(pl.ntiles * pl.G));
 #define DENDSN_FAST_CASE(BL_, L_)                                                   \
   if (pl.BL == BL_ && pl.L == L_ && pl.fast) {                                      \
-    if (pl.KS == 4) return launch_bwd_v<BL_, L_, 4>(grid, ba, v, size_t(pl.lds), stream);           \
-    if constexpr (BL_ <= 4)                                                         \
-      if (pl.KS == 8) return launch_bwd_v<BL_, L_, 8>(grid, ba, v, size_t(pl.lds), stream);         \
+    if (pl.KS == 4) return launch_bwd_v<BL_, L_, 4>(pl, ba, v, stream); \
+    if constexpr (long_stash(BL_, L_, 1, false))                                                         \
+      if (pl.KS == 8) return launch_bwd_v<BL_, L_, 8>(pl, ba, v, stream); \
     return hipErrorInvalidValue;                                                    \
   }
 #define DENDSN_GENERIC_CASE(BL_, L_)                                                \
-  if (pl.BL == BL_ && pl.L == L_ && !pl.fast && pl.KS == DENDSN_GENERIC_KS)         \
-    return launch_bwd_v<BL_, L_, DENDSN_GENERIC_KS>(grid, ba, v, size_t(pl.lds), stream);
+  if (pl.BL == BL_ && pl.L == L_ && !pl.fast && pl.KS == 4) return launch_bwd_v<BL_, L_, 4>(pl, ba, v, stream);
   DENDSN_FAST_BF16_BWD(DENDSN_FAST_CASE)
   DENDSN_GENERIC(DENDSN_GENERIC_CASE)
 #undef DENDSN_FAST_CASE

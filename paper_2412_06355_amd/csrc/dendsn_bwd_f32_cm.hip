@@ -1,8 +1,8 @@
 // Backward-kernel instantiations and dispatch for f32 storage in the
-// channel-major layout (X / grad_x [T, batch, C, P, S], stash capacity 4).
+// channel-major layout (X / grad_x [T, batch, C, P, S]).
 // V: bit 0 = Mexican-hat activation, bit 1 = residual dendrite, bits 2-3 =
 // log2(KC), bit 4 = channel-major, bit 5 = sigmoid
-// surrogate (DENDSN_SG).
+// surrogate (DENDSN_SG); KS: stash steps.
 // Bit 6 of V = Stateless Dendrite (the runtime v passed in: psi | residual << 1 |
 // stateless << 2, mapped by variant_bits).
 #include "dendsn_kernels.h"
@@ -15,23 +15,27 @@ namespace dendsn {
 
 constexpr int kVS = DENDSN_SG << 5;  // surrogate bit of the variant
 
-template <int BL, int L, int KC>
-static hipError_t launch_bwd_cm_v(const dim3& grid, const BwdArgs& ba, int v, size_t lds, hipStream_t stream) {
+template <int BL, int L, int KC, int KS>
+static hipError_t launch_bwd_cm_v(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
   constexpr int VK = 16 | ((KC == 1 ? 0 : (KC == 2 ? 1 : 2)) << 2);
   switch (v & 7) {
 #define DENDSN_V(n) \
-    case n: dendsn_bwd_kernel<float, BL, L, kVS | VK | variant_bits(n), 4><<<grid, dim3(kThreads), lds, stream>>>(ba); break;
+    case n: return launch_bwd<float, BL, L, kVS | VK | variant_bits(n), KS>(pl, ba, stream);
     DENDSN_EACH_VARIANT(DENDSN_V)
 #undef DENDSN_V
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 hipError_t DENDSN_SG_NAME(launch_bwd_f32_cm)(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned>(pl.ntiles * pl.G));
-  if (!pl.cm || pl.KS != 4) return hipErrorInvalidValue;
-#define DENDSN_CASE(BL_, L_, KC_) \
-  if (pl.BL == BL_ && pl.L == L_ && pl.KC == KC_) return launch_bwd_cm_v<BL_, L_, KC_>(grid, ba, v, size_t(pl.lds), stream);
+  if (!pl.cm) return hipErrorInvalidValue;
+#define DENDSN_CASE(BL_, L_, KC_)                                                     \
+  if (pl.BL == BL_ && pl.L == L_ && pl.KC == KC_) {                                   \
+    if (pl.KS == 4) return launch_bwd_cm_v<BL_, L_, KC_, 4>(pl, ba, v, stream); \
+    if constexpr (long_stash(BL_, L_, KC_, true))                                                     \
+      if (pl.KS == 8) return launch_bwd_cm_v<BL_, L_, KC_, 8>(pl, ba, v, stream); \
+    return hipErrorInvalidValue;                                                      \
+  }
   DENDSN_CM(DENDSN_CASE)
 #undef DENDSN_CASE
   return hipErrorInvalidValue;

@@ -1,7 +1,7 @@
 // Backward-kernel instantiations and dispatch for f32 storage with KC = 2 or 4
-// compartments per branch (stash capacity 4).  V: bit 0 = Mexican-hat
+// compartments per branch.  V: bit 0 = Mexican-hat
 // activation, bit 1 = residual dendrite, bits 2-3 = log2(KC), bit 5 = sigmoid
-// surrogate (DENDSN_SG).
+// surrogate (DENDSN_SG); KS: stash steps.
 // Bit 6 of V = Stateless Dendrite (the runtime v passed in: psi | residual << 1 |
 // stateless << 2, mapped by variant_bits).
 #include "dendsn_kernels.h"
@@ -14,29 +14,33 @@ namespace dendsn {
 
 constexpr int kVS = DENDSN_SG << 5;  // surrogate bit of the variant
 
-template <int BL, int L, int KC>
-static hipError_t launch_bwd_kc_v(const dim3& grid, const BwdArgs& ba, int v, size_t lds, hipStream_t stream) {
+template <int BL, int L, int KC, int KS>
+static hipError_t launch_bwd_kc_v(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
   constexpr int VK = (KC == 2 ? 1 : 2) << 2;
   switch (v & 7) {
 #define DENDSN_V(n) \
-    case n: dendsn_bwd_kernel<float, BL, L, kVS | VK | variant_bits(n), 4><<<grid, dim3(kThreads), lds, stream>>>(ba); break;
+    case n: return launch_bwd<float, BL, L, kVS | VK | variant_bits(n), KS>(pl, ba, stream);
     DENDSN_EACH_VARIANT(DENDSN_V)
 #undef DENDSN_V
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 hipError_t DENDSN_SG_NAME(launch_bwd_f32_kc)(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned>(pl.ntiles * pl.G));
-  if (pl.KS != 4) return hipErrorInvalidValue;
-#define DENDSN_FAST_CASE(BL_, L_, KC_) \
-  if (pl.fast && pl.BL == BL_ && pl.L == L_ && pl.KC == KC_) return launch_bwd_kc_v<BL_, L_, KC_>(grid, ba, v, size_t(pl.lds), stream);
-#define DENDSN_GENERIC_CASE(BL_, L_, KC_) \
-  if (!pl.fast && pl.BL == BL_ && pl.L == L_ && pl.KC == KC_) return launch_bwd_kc_v<BL_, L_, KC_>(grid, ba, v, size_t(pl.lds), stream);
+#define DENDSN_CASE(FAST_, BL_, L_, KC_)                                              \
+  if (bool(pl.fast) == FAST_ && pl.BL == BL_ && pl.L == L_ && pl.KC == KC_) {         \
+    if (pl.KS == 4) return launch_bwd_kc_v<BL_, L_, KC_, 4>(pl, ba, v, stream); \
+    if constexpr (long_stash(BL_, L_, KC_, false))                                                     \
+      if (pl.KS == 8) return launch_bwd_kc_v<BL_, L_, KC_, 8>(pl, ba, v, stream); \
+    return hipErrorInvalidValue;                                                      \
+  }
+#define DENDSN_FAST_CASE(BL_, L_, KC_) DENDSN_CASE(true, BL_, L_, KC_)
+#define DENDSN_GENERIC_CASE(BL_, L_, KC_) DENDSN_CASE(false, BL_, L_, KC_)
   DENDSN_KC_FAST_F32(DENDSN_FAST_CASE)
   DENDSN_KC_GENERIC(DENDSN_GENERIC_CASE)
 #undef DENDSN_FAST_CASE
 #undef DENDSN_GENERIC_CASE
+#undef DENDSN_CASE
   return hipErrorInvalidValue;
 }
 

@@ -172,8 +172,23 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
 // A wave-uniform value the compiler cannot prove uniform (a select on loop
 // state inside the lanes' active region) made explicit: as part of a buffer
 // resource it would otherwise be fed to the load through a per-lane loop over
-// distinct values, whose first wait drains every request in flight.
-__device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+// distinct values, whose first wait drains every request in flight.  The empty
+// asm keeps the value in a scalar register: without it a select was folded
+// through the readfirstlane back into a vector register.
+__device__ __forceinline__ uint32_t uniform_u32(uint32_t v) {
+  uint32_t r = __builtin_amdgcn_readfirstlane(v);
+#ifdef __HIP_DEVICE_COMPILE__
+  asm("" : "+s"(r));
+#endif
+  return r;
+}
+
+template <typename P>
+__device__ __forceinline__ const P* uniform_ptr(const P* p) {  // the same for a base address
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = uniform_u32(uint32_t(u)), hi = uniform_u32(uint32_t(u >> 32));
+  return reinterpret_cast<const P*>(hi << 32 | lo);
+}
 
 template <int BL>
 __device__ __forceinline__ void bload_vec(rsrc_t r, uint32_t off, float (&v)[BL], const float*) {
@@ -1240,46 +1255,7 @@ struct BwdLane {  // adjoint state carried backwards through time, and pointers
   float dh_next;
   float lam[E];
   uint32_t* stage;   // the wave's LDS buffer for staged wide rows (see load_pieces)
-  const IO* xbase;   // X of this batch item (uniform)
-  IO* gxbase;
-  const IO* gsbase;
-  const float* gvbase;
 };
-
-// The streamed inputs of one chunk of CS steps.
-template <int E, int CS>
-struct ChunkIn {
-  float x[CS][E];
-  float gs[CS];
-  float gv[CS];
-};
-
-// grad_v_soma rows of a chunk (0 without grad_v_soma); issued with the chunk's
-// other loads so no step waits on a load issued after its stores.
-template <int E, int CS>
-__device__ __forceinline__ void load_chunk_gv(const ScanArgs& a, const LaneOff& lo, const float* gvbase, int c0,
-                                              ChunkIn<E, CS>& in) {
-  if (gvbase) {
-#pragma unroll
-    for (int k = 0; k < CS; ++k) in.gv[k] = __builtin_nontemporal_load(at(gvbase + int64_t(c0 + k) * a.N, lo.v));
-  } else {
-#pragma unroll
-    for (int k = 0; k < CS; ++k) in.gv[k] = 0.0f;
-  }
-}
-
-template <typename IO, int E, int CS, bool CM>
-__device__ __forceinline__ void load_chunk_in(const ScanArgs& a, const LaneOff& lo, const IO* xbase,
-                                              const IO* gsbase, const float* gvbase, int c0, ChunkIn<E, CS>& in) {
-  const int64_t rowX = a.N * a.P;
-#pragma unroll
-  for (int k = 0; k < CS; ++k) {
-    const int64_t t = c0 + k;
-    load_x<E, CM>(xbase + t * rowX, lo.x, a.xes, in.x[k]);
-    in.gs[k] = load_row_one(gsbase + t * a.N, lo.s);
-  }
-  load_chunk_gv<E, CS>(a, lo, gvbase, c0, in);
-}
 
 // A chunk's rows in raw form (see load_raw).  The single-chunk pipeline
 // carries the next neuron's rows this way: a conversion issued next to the
@@ -1292,70 +1268,75 @@ struct ChunkRaw {
   float gv[CS];
 };
 
-template <typename IO, int E, int CS, bool CM, bool GV = true, bool ST = false>
-__device__ __forceinline__ void load_chunk_raw(const ScanArgs& a, const LaneOff& lo, const IO* xbase,
-                                               const IO* gsbase, const float* gvbase, uint32_t gvbytes,
-                                               ChunkRaw<IO, E, CS, CM, ST>& in) {
+// Requests CS rows from x / g / gv (the row of the chunk's first step) on; the
+// row addresses advance by one stride at a time, two scalar additions per row.
+// PART: only the first cs rows exist (cs is wave-uniform); the others are read
+// through buffers of no bytes, so they cost no memory traffic and the number of
+// requests, which the waits are counted by, stays the same.  GV = false:
+// grad_v_soma is known absent, nothing is requested (else absent rows are a
+// buffer of gvbytes = 0 bytes: every load returns 0).  rev = false: X alone.
+// PAIRED: grad_spikes row by row with X (one-chunk neurons of four steps: 0.5-1 %
+// faster); else behind all X rows, which the recompute waits for first (bf16
+// ten-step layer 826 -> 752 us, 64 steps with K = 8: 236 -> 227 us).
+template <typename IO, int E, int CS, bool CM, bool GV = true, bool ST = false, bool PART = false, bool PAIRED = false>
+__device__ __forceinline__ void load_chunk_raw(const ScanArgs& a, const LaneOff& lo, const IO* x, const IO* g,
+                                               const float* gv, uint32_t gvbytes, ChunkRaw<IO, E, CS, CM, ST>& in,
+                                               int cs = CS, bool rev = true) {
   const int64_t rowX = a.N * a.P;
-#pragma unroll
-  for (int k = 0; k < CS; ++k) {
-    if constexpr (ST) bload_pieces<kRawW<IO, E, CM>>(make_rsrc(xbase + k * rowX), lo.xw, in.x[k]);
-    else bload_raw<IO, E, CM>(make_rsrc(xbase + k * rowX), lo.x, a.xes, in.x[k]);
-    const rsrc_t rg = make_rsrc(gsbase + k * a.N);
+  auto bytes = [&](int k, bool want, uint32_t n) { return PART ? uniform_u32(want && k < cs ? n : 0u) : n; };
+  auto load_gs = [&](int k) {
+    const rsrc_t rg = make_rsrc(g, bytes(k, rev, 0xFFFFFFFFu));
     in.gs[k] = sizeof(IO) == 4 ? __builtin_amdgcn_raw_buffer_load_b32(rg, lo.s, 0, kAuxNT)
                                : uint32_t(__builtin_amdgcn_raw_buffer_load_b16(rg, lo.s, 0, kAuxNT));
-  }
-  // grad_v_soma rows (a buffer of no bytes when absent: every load returns 0);
-  // GV = false: known absent, nothing is requested
+    g += a.N;
+  };
 #pragma unroll
-  for (int k = 0; k < CS; ++k)
-    in.gv[k] = GV ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(gvbase + int64_t(k) * a.N, gvbytes),
-                                                                       lo.v, 0, kAuxNT))
+  for (int k = 0; k < CS; ++k) {
+    const rsrc_t rx = make_rsrc(x, bytes(k, true, 0xFFFFFFFFu));
+    if constexpr (ST) bload_pieces<kRawW<IO, E, CM>>(rx, lo.xw, in.x[k]);
+    else bload_raw<IO, E, CM>(rx, lo.x, a.xes, in.x[k]);
+    x += rowX;
+    if (PAIRED) load_gs(k);
+  }
+  if (!PAIRED) {
+#pragma unroll
+    for (int k = 0; k < CS; ++k) load_gs(k);
+  }
+#pragma unroll
+  for (int k = 0; k < CS; ++k) {
+    in.gv[k] = GV ? __uint_as_float(
+                        __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(gv, bytes(k, rev, gvbytes)), lo.v, 0, kAuxNT))
                   : 0.0f;
-}
-
-// The checkpointed state a segment starts from.
-template <int E>
-struct SegStart {
-  float v[E];
-  float h;
-};
-
-template <typename IO, int E, bool SL>
-__device__ __forceinline__ void load_seg_start(const BwdArgs& ba, const LaneOff& lo, int64_t n0, int seg,
-                                               SegStart<E>& st) {
-  const ScanArgs& a = ba.s;
-  if (seg == 0 || SL) {  // the Stateless Dendrite restarts from its input: no state to load
-#pragma unroll
-    for (int j = 0; j < E; ++j) st.v[j] = 0.0f;
-  } else {
-    load_vec<E>(at(ba.ckpt + (int64_t(seg - 1) * a.N + n0) * a.P, lo.c), st.v);
+    gv += a.N;
   }
-  st.h = seg == 0 ? 0.0f : __builtin_nontemporal_load(at(ba.ckh + int64_t(seg - 1) * a.N + n0, lo.v));
 }
 
 // Registers a chunk's recompute leaves for its adjoint pass: the dendritic
 // state before and at each step, H at each step and, for the Mexican hat, the
 // exp(-u^2/2) factor of each step.
-template <int BL, int CS, int V>
+template <int BL, int CS, int V, bool TY = true>
 struct Stash {
   float v[CS + 1][BL * kKC<V>];
   float e[kMH<V> ? CS : 1][BL];
   // one compartment per branch with the Mexican hat: the signed (Vd - xi) / zeta
-  // and psi of each step, as the recompute rounded them
-  float t[kMH<V> && kKC<V> == 1 ? CS : 1][BL];
-  float y[kMH<V> && kKC<V> == 1 ? CS : 1][BL];
+  // and psi of each step, as the recompute rounded them (kTY; else the adjoint
+  // forms both again, with the same operations)
+  static constexpr bool kTY = TY && kMH<V> && kKC<V> == 1;
+  float t[kTY ? CS : 1][BL];
+  float y[kTY ? CS : 1][BL];
   float h[CS];
   float hd0;  // (1 - S) H before the chunk's first step: the decayed term beta multiplies
 };
 
 // Re-runs the chunk's forward steps exactly as the forward kernel did (the same
 // inline step function, so the same bits).  NG: every branch of the lane is on
-// (no gate select; with every branch on the select is the identity).
-template <int BL, int L, int V, int CS, bool NG = false>
+// (no gate select; with every branch on the select is the identity).  PART: only
+// the first cs steps are run (cs is wave-uniform).
+template <int BL, int L, int V, int CS, bool NG = false, bool PART = false, bool TY = true>
 __device__ __forceinline__ void recompute_chunk(const ScanArgs& a, const Branches<BL, kKC<V>>& br, float alpha,
                                                 const float (&v0)[BL * kKC<V>], float h0, bool s0,
-                                                const float (&x)[CS][BL * kKC<V>], Stash<BL, CS, V>& st) {
+                                                const float (&x)[CS][BL * kKC<V>], Stash<BL, CS, V, TY>& st,
+                                                int cs = CS) {
   constexpr int E = BL * kKC<V>;
 #pragma unroll
   for (int j = 0; j < E; ++j) st.v[0][j] = v0[j];
@@ -1366,7 +1347,8 @@ __device__ __forceinline__ void recompute_chunk(const ScanArgs& a, const Branche
   for (int k = 0; k < CS; ++k) {
 #pragma unroll
     for (int j = 0; j < E; ++j) st.v[k + 1][j] = st.v[k][j];
-    constexpr bool ty = kMH<V> && kKC<V> == 1;
+    if (PART && k >= cs) continue;
+    constexpr bool ty = Stash<BL, CS, V, TY>::kTY;
     const float z = dendrite_step<BL, L, V, NG>(st.v[k + 1], x[k], br, alpha, kMH<V> ? st.e[kMH<V> ? k : 0] : nullptr,
                                             ty ? st.t[ty ? k : 0] : nullptr, ty ? st.y[ty ? k : 0] : nullptr);
     soma_step(h, s, z, a.beta, a.vth);
@@ -1375,11 +1357,11 @@ __device__ __forceinline__ void recompute_chunk(const ScanArgs& a, const Branche
 }
 
 // The adjoint recurrences through one chunk, last step first; writes grad_x
-// and accumulates the parameter gradients.  PART: only the first cs steps of
+// (gx: its row of the chunk's first step) and accumulates the parameter gradients.  PART: only the first cs steps of
 // the chunk are real (cs is wave-uniform; the others are padding and skipped).
-template <typename IO, int BL, int L, int V, int CS, bool PART = false, bool ST = false>
+template <typename IO, int BL, int L, int V, int CS, bool PART = false, bool ST = false, bool TY = true>
 __device__ __forceinline__ void reverse_chunk(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
-                                              float alpha, float beta_r, int c0, const Stash<BL, CS, V>& st,
+                                              float alpha, float beta_r, IO* gx, const Stash<BL, CS, V, TY>& st,
                                               const float (&gs)[CS], const float (&gvr)[CS],
                                               BwdLane<IO, BL * kKC<V>>& bl, Accum<BL, BL * kKC<V>>& acc,
                                               int cs = CS) {
@@ -1387,8 +1369,9 @@ __device__ __forceinline__ void reverse_chunk(const BwdArgs& ba, const LaneOff& 
   const ScanArgs& a = ba.s;
   const int64_t rowX = a.N * a.P;
   const float beta = a.beta, vth = a.vth;
+  gx += (CS - 1) * rowX;  // grad_x row of step k, walking down
 #pragma unroll
-  for (int k = CS - 1; k >= 0; --k) {
+  for (int k = CS - 1; k >= 0; gx -= rowX, --k) {
     if (PART && k >= cs) continue;
     const float hk = st.h[k];
     const bool sk = hk >= vth;
@@ -1403,12 +1386,13 @@ __device__ __forceinline__ void reverse_chunk(const BwdArgs& ba, const LaneOff& 
 #pragma unroll
     for (int j = 0; j < BL; ++j) {
       if constexpr (KC == 1) {
-        const float tt = kMH<V> ? st.t[kMH<V> ? k : 0][j] : (st.v[k + 1][j] - br.xi[j]) * br.rz[j];
+        constexpr bool ty = Stash<BL, CS, V, TY>::kTY;
+        const float tt = ty ? st.t[ty ? k : 0][j] : (st.v[k + 1][j] - br.xi[j]) * br.rz[j];
         const float dhk = dh * br.krz[j];
         float y, r;  // psi(u), and r = kappa* dH psi'(u) sgn(Vd - xi) / zeta
         if constexpr (kMH<V>) {
           const float e = st.e[k][j];
-          y = st.y[k][j];
+          y = ty ? st.y[ty ? k : 0][j] : fmaf(-(tt * tt), e, e);
           r = (tt * fmaf(2.0f, e, y)) * -dhk;          // psi'(u) sgn = tt (q - 3) e = -tt (y + 2 e)
         } else {
           y = fabsf(tt);
@@ -1451,128 +1435,19 @@ __device__ __forceinline__ void reverse_chunk(const BwdArgs& ba, const LaneOff& 
         acc.z[j] = fmaf(-dhk, gzu, acc.z[j]);     // -kappa* dH psi'(u) u / zeta
       }
     }
-    if constexpr (ST) store_gx_staged<IO, E>(bl.gxbase + int64_t(c0 + k) * rowX, lo.xw, gxo, bl.stage);
-    else store_gx<E, kCM<V>>(bl.gxbase + int64_t(c0 + k) * rowX, lo.x, a.xes, gxo);
+    if constexpr (ST) store_gx_staged<IO, E>(gx, lo.xw, gxo, bl.stage);
+    else store_gx<E, kCM<V>>(gx, lo.x, a.xes, gxo);
     bl.dh_next = dh;
   }
 }
 
-template <typename IO, int BL, int L, int V, int CS, bool ST = false>
-__device__ __forceinline__ void bwd_chunk(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
-                                          float alpha, float beta_r, int c0, const float (&v0)[BL * kKC<V>],
-                                          float h0, bool s0, const ChunkIn<BL * kKC<V>, CS>& in,
-                                          BwdLane<IO, BL * kKC<V>>& bl, Accum<BL, BL * kKC<V>>& acc) {
-  Stash<BL, CS, V> st;
-  recompute_chunk<BL, L, V, CS>(ba.s, br, alpha, v0, h0, s0, in.x, st);
-  reverse_chunk<IO, BL, L, V, CS, false, ST>(ba, lo, br, alpha, beta_r, c0, st, in.gs, in.gv, bl, acc);
-}
-
-// Runs the forward from (vd, h, s) at step t_from up to (not including) t_to.
-template <typename IO, int BL, int L, int V>
-__device__ __forceinline__ void advance(const ScanArgs& a, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
-                                        float alpha, const IO* xbase, int t_from, int t_to,
-                                        float (&vd)[BL * kKC<V>], float& h, bool& s) {
-  constexpr int E = BL * kKC<V>;
-  const int64_t rowX = a.N * a.P;
-  for (int t = t_from; t < t_to; ++t) {
-    float xv[E];
-    load_x<E, kCM<V>>(xbase + int64_t(t) * rowX, lo.x, a.xes, xv);
-    const float z = dendrite_step<BL, L, V>(vd, xv, br, alpha);
-    soma_step(h, s, z, a.beta, a.vth);
-  }
-}
-
-// Loads a chunk of CS steps and runs it (used for every chunk but a prefetched one).
-template <typename IO, int BL, int L, int V, int CS, bool ST = false>
-__device__ __forceinline__ void load_and_run_chunk(const BwdArgs& ba, const LaneOff& lo,
-                                                   const Branches<BL, kKC<V>>& br, float alpha, float beta_r,
-                                                   int t0, int c0, const SegStart<BL * kKC<V>>& ss,
-                                                   BwdLane<IO, BL * kKC<V>>& bl, Accum<BL, BL * kKC<V>>& acc) {
-  constexpr int E = BL * kKC<V>;
-  ChunkIn<E, CS> in;
-  load_chunk_in<IO, E, CS, kCM<V>>(ba.s, lo, bl.xbase, bl.gsbase, bl.gvbase, c0, in);
-  float v[E];
-#pragma unroll
-  for (int j = 0; j < E; ++j) v[j] = ss.v[j];
-  float h = ss.h;
-  bool s = ss.h >= ba.s.vth && t0 > 0;
-  advance<IO, BL, L, V>(ba.s, lo, br, alpha, bl.xbase, t0, c0, v, h, s);
-  bwd_chunk<IO, BL, L, V, CS, ST>(ba, lo, br, alpha, beta_r, c0, v, h, s, in, bl, acc);
-}
-
-// Chunk plan of a segment [t0, t1): whole KS-step chunks from t0, then the
-// remainder in descending powers of two, placed from the top down; visited
-// from the last step backwards.  A neuron's first visited chunk is the top of
-// its last segment; it is a full KS chunk exactly when that segment's length
-// is a multiple of KS, and only then is it prefetched.
-template <typename IO, int BL, int L, int V, int KS, bool ST = false>
-__device__ __forceinline__ void backward_neuron(const BwdArgs& ba, const LaneOff& lo, int64_t bt,
-                                                const Branches<BL, kKC<V>>& br, float alpha,
-                                                Accum<BL, BL * kKC<V>>& acc, uint32_t* stage) {
-  constexpr int E = BL * kKC<V>;
-  const ScanArgs& a = ba.s;
-  const int T = int(a.T);
-  const int K = a.K;
-  const float beta_r = ba.detach ? 0.0f : a.beta;
-  const int64_t n0 = bt * a.M;  // first neuron of this batch item (wave-uniform)
-  BwdLane<IO, E> bl;
-  bl.xbase = static_cast<const IO*>(a.x) + n0 * a.P;
-  bl.gxbase = static_cast<IO*>(ba.gx) + n0 * a.P;
-  bl.gsbase = static_cast<const IO*>(ba.gspk) + n0;
-  bl.gvbase = ba.gv ? ba.gv + n0 : nullptr;
-  bl.dh_next = 0.0f;
-  bl.stage = stage;
-#pragma unroll
-  for (int j = 0; j < E; ++j) bl.lam[j] = 0.0f;
-
-  const int nseg = (T + K - 1) / K;
-  for (int seg = nseg - 1; seg >= 0; --seg) {
-    const int t0 = seg * K;
-    const int t1 = min(T, t0 + K);
-    SegStart<E> ss;
-    load_seg_start<IO, E, kSL<V>>(ba, lo, n0, seg, ss);
-    // Chunks: the remainder (len mod KS) first, in descending powers of two
-    // from t0, then whole KS-step chunks; visited from the last one back.  A
-    // chunk re-runs the forward from t0 up to its first step, so putting the
-    // short pieces first keeps that re-advance as short as possible.
-    const int len = t1 - t0;
-    const int nfull = len / KS;
-    const int rem = len - nfull * KS;
-    for (int ch = nfull - 1; ch >= 0; --ch) {
-      const int c0 = t0 + rem + ch * KS;
-      ChunkIn<E, KS> in;
-      load_chunk_in<IO, E, KS, kCM<V>>(a, lo, bl.xbase, bl.gsbase, bl.gvbase, c0, in);
-      float v[E];
-#pragma unroll
-      for (int j = 0; j < E; ++j) v[j] = ss.v[j];
-      float h = ss.h;
-      bool s = ss.h >= a.vth && t0 > 0;
-      advance<IO, BL, L, V>(a, lo, br, alpha, bl.xbase, t0, c0, v, h, s);
-      bwd_chunk<IO, BL, L, V, KS, ST>(ba, lo, br, alpha, beta_r, c0, v, h, s, in, bl, acc);
-    }
-    // remainder pieces fill [t0, t0 + rem) with the largest on top and the
-    // smallest at t0 (their re-advances then sum to the least); top one first
-    int top = t0 + rem;
-#pragma unroll
-    for (int cs = KS / 2; cs >= 1; cs /= 2) {
-      if (rem & cs) {
-        const int c0 = top - cs;
-        if (cs == 4) load_and_run_chunk<IO, BL, L, V, (KS >= 8 ? 4 : 1), ST>(ba, lo, br, alpha, beta_r, t0, c0, ss, bl, acc);
-        else if (cs == 2) load_and_run_chunk<IO, BL, L, V, (KS >= 4 ? 2 : 1), ST>(ba, lo, br, alpha, beta_r, t0, c0, ss, bl, acc);
-        else load_and_run_chunk<IO, BL, L, V, 1, ST>(ba, lo, br, alpha, beta_r, t0, c0, ss, bl, acc);
-        top = c0;
-      }
-    }
-  }
-}
-
-// The common short-sequence case: T == KS, so every neuron is one chunk that
-// starts from the zero state.  Software-pipelined over the lane's neurons: the
-// next neuron's rows are requested as soon as this neuron's rows are widened to
-// float, so they stream in during its recompute and adjoint pass.  FAST: no
-// branch of the wave is gated off (no gate select, see recompute_chunk) and no
-// grad_v_soma is given (no loads of it).
-template <typename IO, int BL, int L, int V, int KS, bool FAST = false, bool ST = false>
+// The short-sequence case: T <= KS, so every neuron is one chunk that starts
+// from the zero state (PART: T < KS, or known at run time only).  Software-
+// pipelined over the lane's neurons: the next neuron's rows are requested as
+// soon as this neuron's rows are widened to float, so they stream in during its
+// recompute and adjoint pass.  FAST: no branch of the wave is gated off (no
+// gate select, see recompute_chunk) and no grad_v_soma is given (no loads of it).
+template <typename IO, int BL, int L, int V, int KS, bool FAST = false, bool ST = false, bool PART = false>
 __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const LaneOff& lo,
                                                    const Branches<BL, kKC<V>>& br, float alpha, int64_t bt0,
                                                    int nk, Accum<BL, BL * kKC<V>>& acc, uint32_t* stage) {
@@ -1582,13 +1457,14 @@ __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const Lane
   // The lane's nw positions of each item in turn, then the next item (Walk).
   const Walk wk = make_walk<L, kCM<V>>(a, int64_t(a.ways) * a.M);
   const int nvis = wk.nw * nk;
+  const int cs = PART ? int(a.T) : KS;
   int64_t n0 = bt0 * a.M, nx0 = bt0 * a.M * a.P;
   const IO* x = static_cast<const IO*>(a.x);
   const IO* g = static_cast<const IO*>(ba.gspk);
   if (nvis <= 0) return;
   constexpr int W = kRawW<IO, E, kCM<V>>;
   ChunkRaw<IO, E, KS, kCM<V>, ST> cur;
-  load_chunk_raw<IO, E, KS, kCM<V>, !FAST, ST>(a, lo, x + nx0, g + n0, ba.gvz + n0, ba.gvn, cur);
+  load_chunk_raw<IO, E, KS, kCM<V>, !FAST, ST, PART, !PART>(a, lo, x + nx0, g + n0, ba.gvz + n0, ba.gvn, cur, cs);
   // Every later wait is then counted from loads issued inside the loop, whose
   // next-neuron loads are unconditional (the last neuron runs after it).
   __builtin_amdgcn_s_waitcnt(kWaitVmem);
@@ -1596,11 +1472,8 @@ __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const Lane
   auto item = [&](const ChunkRaw<IO, E, KS, kCM<V>, ST>& in, bool more, ChunkRaw<IO, E, KS, kCM<V>, ST>& nxt) {
     BwdLane<IO, E> bl;
     bl.stage = stage;
-    bl.xbase = x + nx0;
-    bl.gxbase = static_cast<IO*>(ba.gx) + nx0;
-    bl.gsbase = g + n0;
-    bl.gvbase = ba.gv ? ba.gv + n0 : nullptr;
     bl.dh_next = 0.0f;
+    IO* const gx = static_cast<IO*>(ba.gx) + nx0;
     float xin[KS][E], gsv[KS], zero[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) { bl.lam[j] = 0.0f; zero[j] = 0.0f; }
@@ -1619,14 +1492,15 @@ __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const Lane
       if (last_w) w = 0;
       n0 += last_w ? wk.dn_item : wk.dn;
       nx0 += last_w ? wk.dnx_item : wk.dnx;
-      load_chunk_raw<IO, E, KS, kCM<V>, !FAST, ST>(a, lo, x + nx0, g + n0, ba.gvz + n0, ba.gvn, nxt);
+      load_chunk_raw<IO, E, KS, kCM<V>, !FAST, ST, PART, !PART>(a, lo, x + nx0, g + n0, ba.gvz + n0, ba.gvn, nxt, cs);
     }
     // Keeps the requests at this point: left to itself the scheduler sank them
     // below most of the recompute (bf16 layers' backward 2-6 % slower).
     __builtin_amdgcn_sched_barrier(0);
-    Stash<BL, KS, V> st;
-    recompute_chunk<BL, L, V, KS, FAST>(a, br, alpha, zero, 0.0f, false, xin, st);
-    reverse_chunk<IO, BL, L, V, KS, false, ST>(ba, lo, br, alpha, beta_r, 0, st, gsv, gvv, bl, acc);
+    // chunks of 8 steps leave no registers for psi (a third wave per SIMD instead)
+    Stash<BL, KS, V, (KS <= 4)> st;
+    recompute_chunk<BL, L, V, KS, FAST, PART>(a, br, alpha, zero, 0.0f, false, xin, st, cs);
+    reverse_chunk<IO, BL, L, V, KS, PART, ST>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cs);
   };
   for (int i = 0; i + 1 < nvis; ++i) {
     ChunkRaw<IO, E, KS, kCM<V>, ST> nxt;
@@ -1636,126 +1510,211 @@ __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const Lane
   item(cur, false, cur);
 }
 
-// The Stateless Dendrite over several checkpoint segments of at most KS steps
-// (K <= KS < T).  Its compartments carry no state from step to step, so a
-// segment restarts from its checkpointed somatic potential and its own inputs,
-// and nothing but dH crosses a segment boundary (in reverse time, within one
-// neuron).  Every (neuron, segment) visit is one chunk of KS rows, the rows past
-// the segment's end padding (they read one cache line of the segment's first
-// row per wave, compute, and are skipped by the adjoint pass).  Software-
-// pipelined over the lane's visits like single_chunk_items: the next visit's
-// rows and checkpoint are requested right after this visit's recompute, so they
-// stream in while its adjoint pass runs.  Visit order: batch items, the lane's
-// positions of each item, and each neuron's segments from last to first.
-template <typename IO, int E, int CS, bool CM, bool ST = false>
-struct SegRaw {
+// Every other sequence: segments of K steps between checkpoints, visited from
+// last to first, each cut into chunks of KS steps with the remainder first.
+// Every chunk is one visit of the memory pipeline: the next visit's rows are
+// requested before this visit computes, so they stream in meanwhile.  A segment
+// of one chunk (K <= KS) is visited once.  A longer one is first run forward up
+// to its last chunk (advance visits, X rows only), each chunk's starting state
+// going to the lane's LDS slots; then every chunk, last to first, is recomputed
+// from its slot and reversed.  So X is read at most twice, whatever T / KS
+// (before, each chunk re-ran the forward from the segment's start with no load
+// in flight: T^2 / KS reads).  Where the slots do not hold every chunk's start,
+// they hold every (1 << bsh)-th one, and a chunk between two advances from the
+// slot below it.  Rows past a short chunk's end go through buffers of no bytes
+// and are skipped by the arithmetic.
+template <typename IO, int E, int CS, bool CM, bool ST, bool SL>
+struct VisitRaw {
   ChunkRaw<IO, E, CS, CM, ST> in;
-  float h0;  // somatic potential before the segment (0 for the first)
+  float v0[SL ? 1 : E];  // checkpointed compartment states before the segment
+  float h0;              // and somatic potential (0 for the first segment)
 };
 
-template <typename IO, int BL, int L, int V, int KS, bool GV = true, bool ST = false>
-__device__ __forceinline__ void load_segment_raw(const BwdArgs& ba, const LaneOff& lo, int64_t n0, int64_t nx0,
-                                                 int seg, SegRaw<IO, BL * kKC<V>, KS, kCM<V>, ST>& r) {
-  constexpr int E = BL * kKC<V>;
-  const ScanArgs& a = ba.s;
-  const int64_t rowX = a.N * a.P;
-  const int T = int(a.T), K = a.K;
-  const int c0 = seg * K;
-  const int len = min(K, T - c0);
-  const IO* x = static_cast<const IO*>(a.x) + nx0;
-  const IO* g = static_cast<const IO*>(ba.gspk) + n0;
-#pragma unroll
-  for (int k = 0; k < KS; ++k) {
-    const bool real = k < len;
-    const int t = real ? c0 + k : c0;
-    if constexpr (ST) bload_pieces<kRawW<IO, E, kCM<V>>>(make_rsrc(x + int64_t(t) * rowX), real ? lo.xw : 0u, r.in.x[k]);
-    else bload_raw<IO, E, kCM<V>>(make_rsrc(x + int64_t(t) * rowX), real ? lo.x : 0u, a.xes, r.in.x[k]);
-    const rsrc_t rg = make_rsrc(g + int64_t(t) * a.N);
-    const uint32_t os = real ? lo.s : 0u;
-    r.in.gs[k] = sizeof(IO) == 4 ? __builtin_amdgcn_raw_buffer_load_b32(rg, os, 0, kAuxNT)
-                                 : uint32_t(__builtin_amdgcn_raw_buffer_load_b16(rg, os, 0, kAuxNT));
-    r.in.gv[k] = GV ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                          make_rsrc(ba.gvz + n0 + int64_t(t) * a.N, uniform_u32(real ? ba.gvn : 0u)), lo.v, 0,
-                          kAuxNT))
-                    : 0.0f;  // GV = false: known absent, nothing is requested
-  }
-  // checkpointed H after step c0 - 1 (a buffer of no bytes for the first segment)
-  const float* hp = seg > 0 ? ba.ckh + int64_t(seg - 1) * a.N + n0 : ba.gvz;
-  r.h0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(hp, uniform_u32(seg > 0 ? 0xFFFFFFFFu : 0u)),
-                                                                lo.v, 0, kAuxNT));
-}
+// Wave-uniform place in the visit order: neuron (its [T, N] index and X offset),
+// segment, position index, the chunk being run and the chunk that its run leads
+// to (equal where the chunk is reversed, else the visit only advances).
+struct VisitAt {
+  int64_t n0, nx0;
+  int seg, w, i, j;
+  int c0, cs;   // first step and length of chunk i
+  bool first;   // the visit starts its run (its state comes from a checkpoint or a slot)
+  bool last;    // the segment's last chunk is being reversed
+};
 
-template <typename IO, int BL, int L, int V, int KS, bool FAST = false, bool ST = false>
-__device__ __forceinline__ void stateless_segment_items(const BwdArgs& ba, const LaneOff& lo,
-                                                        const Branches<BL, kKC<V>>& br, int64_t bt0, int nk,
-                                                        Accum<BL, BL * kKC<V>>& acc, uint32_t* stage) {
-  constexpr int E = BL * kKC<V>;
-  constexpr int W = kRawW<IO, E, kCM<V>>;
-  const ScanArgs& a = ba.s;
-  const float beta_r = ba.detach ? 0.0f : a.beta;
-  const int T = int(a.T), K = a.K;
-  const int nseg = (T + K - 1) / K;
-  const Walk wk = make_walk<L, kCM<V>>(a, int64_t(a.ways) * a.M);
-  const int nvis = wk.nw * nk * nseg;
-  if (nvis <= 0) return;
-  // two cursors over the same visit sequence: the visit being loaded, and the
-  // one being computed (wave-uniform)
-  struct Cursor {
-    int64_t n0, nx0;
-    int seg, w;
-  };
-  auto next = [&](Cursor& c) {
-    if (c.seg > 0) { --c.seg; return; }
-    c.seg = nseg - 1;
+// Chunk i of segment seg: i = 0 holds the remainder.
+template <int KS>
+__device__ __forceinline__ void place_chunk(const ScanArgs& a, VisitAt& c) {
+  const int t0 = c.seg * a.K, len = min(a.K, int(a.T) - t0);
+  const int rem = len - ((len - 1) / KS) * KS;  // 1 .. KS steps in chunk 0
+  c.c0 = c.i > 0 ? t0 + rem + (c.i - 1) * KS : t0;
+  c.cs = c.i > 0 ? KS : rem;
+}
+// The start of a segment's first run, to its last chunk.
+template <int KS>
+__device__ __forceinline__ void enter_segment(const ScanArgs& a, VisitAt& c) {
+  c.j = (min(a.K, int(a.T) - c.seg * a.K) - 1) / KS;
+  c.i = 0;
+  c.first = c.last = true;
+  place_chunk<KS>(a, c);
+}
+// The next visit; true where it is another neuron's first.  FULL: every segment
+// is one chunk of KS steps.
+template <int KS, bool FULL>
+__device__ __forceinline__ bool next_visit(const ScanArgs& a, const Walk& wk, int nseg, VisitAt& c) {
+  if (!FULL && c.j > 0) {
+    if (c.i < c.j) {  // on towards chunk j
+      ++c.i;
+      c.first = false;
+      place_chunk<KS>(a, c);
+      return false;
+    }
+    --c.j;  // the chunk below, from the slot at or below it
+    c.i = (c.j >> a.bsh) << a.bsh;
+    c.first = true;
+    c.last = false;
+    place_chunk<KS>(a, c);
+    return false;
+  }
+  const bool neuron = c.seg == 0;
+  if (neuron) {
+    c.seg = nseg;
     const bool last_w = ++c.w == wk.nw;
     if (last_w) c.w = 0;
     c.n0 += last_w ? wk.dn_item : wk.dn;
     c.nx0 += last_w ? wk.dnx_item : wk.dnx;
-  };
-  Cursor ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0};
-  Cursor cp = ld;
-  SegRaw<IO, E, KS, kCM<V>, ST> cur;
-  load_segment_raw<IO, BL, L, V, KS, !FAST, ST>(ba, lo, ld.n0, ld.nx0, ld.seg, cur);
-  next(ld);
-  // Every later wait is then counted from loads issued inside the loop, whose
-  // next-visit loads are unconditional (the last visit runs after it).
+  }
+  --c.seg;
+  if constexpr (FULL) c.c0 = c.seg * KS;
+  else enter_segment<KS>(a, c);
+  return neuron;
+}
+
+// The next visit's rows are requested before this visit computes; where a
+// stateful fp32 lane's stash fills the registers, after it (64 steps, K = 8:
+// 236 -> 227 us; ten compartments spilled with rows in flight).
+template <typename IO, int V>
+constexpr bool kEarlyVisit = sizeof(IO) == 2 || kSL<V>;
+
+// more = false: past the last visit, everything through buffers of no bytes
+// (early requests are unconditional, see the waits below).
+template <typename IO, int BL, int L, int V, int KS, bool GV, bool ST, bool FULL>
+__device__ __forceinline__ void load_visit(const BwdArgs& ba, const LaneOff& lo, const VisitAt& c, bool more,
+                                           VisitRaw<IO, BL * kKC<V>, KS, kCM<V>, ST, kSL<V>>& r) {
+  constexpr int E = BL * kKC<V>;
+  const ScanArgs& a = ba.s;
+  // The state checkpointed after step c0 - 1, where a run starts from it (else a
+  // buffer of no bytes: zeros, as for the first segment).
+  const bool ck = more && c.seg > 0 && (FULL || c.i == 0);
+  const int64_t at_ck = ck ? int64_t(c.seg - 1) * a.N + c.n0 : 0;
+  const uint32_t nb = uniform_u32(ck ? 0xFFFFFFFFu : 0u);
+  if constexpr (!kSL<V>)
+    bload_vec<E>(make_rsrc(uniform_ptr(ba.ckpt + at_ck * a.P), nb), lo.c, r.v0, static_cast<const float*>(nullptr));
+  r.h0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(uniform_ptr(ba.ckh + at_ck), nb), lo.v, 0, kAuxNT));
+  const int64_t row = int64_t(c.c0) * a.N;
+  load_chunk_raw<IO, E, KS, kCM<V>, GV, ST, !(FULL && !kEarlyVisit<IO, V>)>(a, lo, static_cast<const IO*>(a.x) + c.nx0 + row * a.P,
+                                                  static_cast<const IO*>(ba.gspk) + c.n0 + row,
+                                                  ba.gvz + c.n0 + row, ba.gvn, r.in, !more ? 0 : (FULL ? KS : c.cs),
+                                                  FULL || c.i == c.j);
+}
+
+template <typename IO, int BL, int L, int V, int KS, bool FAST, bool ST, bool FULL>
+__device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
+                                            float alpha, int64_t bt0, int nk, Accum<BL, BL * kKC<V>>& acc,
+                                            uint32_t* stage, float* bnd) {
+  constexpr int E = BL * kKC<V>;
+  constexpr int W = kRawW<IO, E, kCM<V>>;
+  constexpr int SE = kSL<V> ? 0 : E;  // compartment states kept per slot
+  constexpr bool kEarly = kEarlyVisit<IO, V>;
+  using Raw = VisitRaw<IO, E, KS, kCM<V>, ST, kSL<V>>;
+  const ScanArgs& a = ba.s;
+  const float beta_r = ba.detach ? 0.0f : a.beta;
+  const int nseg = (int(a.T) + a.K - 1) / a.K;
+  const Walk wk = make_walk<L, kCM<V>>(a, int64_t(a.ways) * a.M);
+  int todo = wk.nw * nk;  // neurons whose last visit is still to be requested
+  if (todo <= 0) return;
+  const int bsh = a.bsh;
+  bnd += threadIdx.x;
+  VisitAt ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0, 0, 0, 0, 0, true, true};
+  enter_segment<KS>(a, ld);
+  VisitAt cp = ld;
+  Raw cur;
+  load_visit<IO, BL, L, V, KS, !FAST, ST, FULL>(ba, lo, ld, true, cur);
+  todo -= next_visit<KS, FULL>(a, wk, nseg, ld) ? 1 : 0;
+  // Every later wait is then counted from loads issued inside the loop, which
+  // are unconditional (past the last visit, rows of no bytes).
   __builtin_amdgcn_s_waitcnt(kWaitVmem);
   BwdLane<IO, E> bl;
   bl.dh_next = 0.0f;
   bl.stage = stage;
-  auto visit = [&](const SegRaw<IO, E, KS, kCM<V>, ST>& in, bool more, SegRaw<IO, E, KS, kCM<V>, ST>& nxt) {
-    const int c0 = cp.seg * K;
-    const int len = min(K, T - c0);
-    bl.gxbase = static_cast<IO*>(ba.gx) + cp.nx0;
-    if (cp.seg == nseg - 1) bl.dh_next = 0.0f;  // the neuron's last segment: nothing after it
-    float xin[KS][E], gsv[KS], zero[E];
+  float v[E], h = 0.0f;  // state before the visit's chunk
 #pragma unroll
-    for (int j = 0; j < E; ++j) zero[j] = 0.0f;
+  for (int j = 0; j < E; ++j) bl.lam[j] = v[j] = 0.0f;
+  bool s = false;
+  auto visit = [&](const Raw& in, bool more, Raw& nxt) {
+    if (FULL || cp.first) {
+      if (FULL || cp.i == 0) {
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = kSL<V> ? 0.0f : in.v0[kSL<V> ? 0 : j];
+        h = in.h0;
+        s = cp.seg > 0 && h >= a.vth;
+      } else {
+        const float* b = bnd + ((cp.i >> bsh) - 1) * ((SE + 1) * kThreads);
+#pragma unroll
+        for (int j = 0; j < SE; ++j) v[j] = b[j * kThreads];
+        h = b[SE * kThreads];
+        s = h >= a.vth;
+      }
+    }
+    float xin[KS][E], gsv[KS], gvv[KS];
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
       uint32_t raw[W];
       slot_to_lane<W, ST>(in.in.x[k], stage, raw);
       raw_to_float<IO, E>(raw, xin[k]);
       gsv[k] = raw_to_float<IO>(in.in.gs[k]);
+      gvv[k] = FAST ? 0.0f : in.in.gv[k];
     }
-    float gvv[KS];
+    auto request = [&] {
+      load_visit<IO, BL, L, V, KS, !FAST, ST, FULL>(ba, lo, ld, more, nxt);
+      todo -= next_visit<KS, FULL>(a, wk, nseg, ld) ? 1 : 0;
+    };
+    if (kEarly) request();
+    __builtin_amdgcn_sched_barrier(0);
+    if (FULL || cp.i == cp.j) {
+      if ((FULL || cp.last) && cp.seg == nseg - 1) {  // the neuron's last chunk: nothing after it
+        bl.dh_next = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) gvv[k] = FAST ? 0.0f : in.in.gv[k];
-    Stash<BL, KS, V> st;
-    recompute_chunk<BL, L, V, KS, FAST>(a, br, 0.0f, zero, in.h0, cp.seg > 0 && in.h0 >= a.vth, xin, st);
-    if (more) {
-      load_segment_raw<IO, BL, L, V, KS, !FAST, ST>(ba, lo, ld.n0, ld.nx0, ld.seg, nxt);
-      next(ld);
+        for (int j = 0; j < E; ++j) bl.lam[j] = 0.0f;
+      }
+      IO* const gx = static_cast<IO*>(ba.gx) + cp.nx0 + int64_t(cp.c0) * (a.N * a.P);
+      Stash<BL, KS, V, (KS <= 4 || sizeof(IO) == 4)> st;
+      recompute_chunk<BL, L, V, KS, FAST, !FULL>(a, br, alpha, v, h, s, xin, st, cp.cs);
+      reverse_chunk<IO, BL, L, V, KS, !FULL, ST>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cp.cs);
+    } else {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        if (k >= cp.cs) continue;
+        const float z = dendrite_step<BL, L, V, FAST>(v, xin[k], br, alpha);
+        soma_step(h, s, z, a.beta, a.vth);
+      }
+      const int n = cp.i + 1;  // the chunk that starts here
+      if (n < cp.j && (n >> bsh) << bsh == n) {  // (chunk j is next: its state is here)
+        float* b = bnd + ((n >> bsh) - 1) * ((SE + 1) * kThreads);
+#pragma unroll
+        for (int j = 0; j < SE; ++j) b[j * kThreads] = v[j];
+        b[SE * kThreads] = h;
+      }
     }
-    reverse_chunk<IO, BL, L, V, KS, true, ST>(ba, lo, br, 0.0f, beta_r, c0, st, gsv, gvv, bl, acc, len);
-    next(cp);
+    next_visit<KS, FULL>(a, wk, nseg, cp);
+    if (!kEarly) __builtin_amdgcn_sched_barrier(0);
+    if (!kEarly && more) request();
   };
-  for (int i = 0; i + 1 < nvis; ++i) {
-    SegRaw<IO, E, KS, kCM<V>, ST> nxt;
-    visit(cur, true, nxt);
+  for (bool more = true; more;) {
+    more = todo > 0;
+    Raw nxt;
+    visit(cur, more, nxt);
     cur = nxt;
   }
-  visit(cur, false, cur);
 }
 
 // The registers of a stateful wide visit in flight (its X rows and
@@ -1768,91 +1727,83 @@ struct SegSmall {
   float h0;  // somatic potential before the segment (0 for the first)
 };
 
-// Requests visit (n0, nx0, seg): X rows and the checkpointed compartment state
-// into `area` (rows past the segment's end are not fetched), the rest into r.
+// Requests visit c: X rows and, where a run starts from it, the checkpointed
+// compartment state into `area` (rows past the chunk's end are not fetched), the
+// rest into r.
 template <typename IO, int BL, int V, int KS, bool FAST>
-__device__ __forceinline__ void issue_wide_segment(const BwdArgs& ba, const LaneOff& lo, int64_t n0, int64_t nx0,
-                                                   int seg, uint32_t* area, SegSmall<KS>& r) {
+__device__ __forceinline__ void issue_wide_visit(const BwdArgs& ba, const LaneOff& lo, const VisitAt& c,
+                                                 uint32_t* area, SegSmall<KS>& r) {
   constexpr int W = BL * kKC<V>;
   constexpr int RD = kDmaDw<W>;
   const ScanArgs& a = ba.s;
   const int64_t rowX = a.N * a.P;
-  const int T = int(a.T), K = a.K;
-  const int c0 = seg * K;
-  const int len = min(K, T - c0);
-  const IO* x = static_cast<const IO*>(a.x) + nx0;
-  const IO* g = static_cast<const IO*>(ba.gspk) + n0;
+  const IO* x = static_cast<const IO*>(a.x) + c.nx0;
+  const IO* g = static_cast<const IO*>(ba.gspk) + c.n0;
+  const bool rev = c.i == c.j;
 #pragma unroll
   for (int k = 0; k < KS; ++k) {
-    const bool real = k < len;
-    const int t = real ? c0 + k : c0;
+    const bool real = k < c.cs;
+    const int t = real ? c.c0 + k : c.c0;
     if (real) dma_pieces<W>(make_rsrc(x + int64_t(t) * rowX), lo.xw, area + k * RD);
-    r.gs[k] = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(g + int64_t(t) * a.N), real ? lo.s : 0u, 0, kAuxNT);
+    r.gs[k] = __builtin_amdgcn_raw_buffer_load_b32(
+        make_rsrc(g + int64_t(t) * a.N, uniform_u32(real && rev ? 0xFFFFFFFFu : 0u)), lo.s, 0, kAuxNT);
     r.gv[k] = FAST ? 0.0f
                    : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                         make_rsrc(ba.gvz + n0 + int64_t(t) * a.N, uniform_u32(real ? ba.gvn : 0u)), lo.v, 0,
+                         make_rsrc(ba.gvz + c.n0 + int64_t(t) * a.N, uniform_u32(real && rev ? ba.gvn : 0u)), lo.v, 0,
                          kAuxNT));
   }
-  if (seg > 0) dma_pieces<W>(make_rsrc(ba.ckpt + (int64_t(seg - 1) * a.N + n0) * a.P), lo.xw, area + KS * RD);
-  const float* hp = seg > 0 ? ba.ckh + int64_t(seg - 1) * a.N + n0 : ba.gvz;
-  r.h0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(hp, uniform_u32(seg > 0 ? 0xFFFFFFFFu : 0u)),
+  const bool ck = c.seg > 0 && c.i == 0;
+  if (ck) dma_pieces<W>(make_rsrc(ba.ckpt + (int64_t(c.seg - 1) * a.N + c.n0) * a.P), lo.xw, area + KS * RD);
+  const float* hp = uniform_ptr(ck ? ba.ckh + int64_t(c.seg - 1) * a.N + c.n0 : ba.gvz);
+  r.h0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(hp, uniform_u32(ck ? 0xFFFFFFFFu : 0u)),
                                                                 lo.v, 0, kAuxNT));
 }
 
 // The stateful dendrite's wide fp32 lanes (a lane row of more than 16 bytes,
-// e.g. ten compartments), every segment one chunk (K <= KS): pipelined over the
-// lane's (neuron, segment) visits in the Stateless pipeline's order, but the
-// next visit's X rows and checkpointed compartment state travel by LDS DMA
-// (dma_pieces) into the wave's LDS area, where they wait without registers:
-// the stash of a wide stateful neuron leaves none for rows in flight.  The
-// small per-neuron rows (grad_spikes, grad_v_soma, the checkpointed H) ride in
-// registers, and grad_x leaves as whole pieces through the wave's `stage`
-// buffer (store_gx_staged).  The dendritic adjoint lam and dH cross segment
-// boundaries in reverse time within one neuron and restart at its last
-// segment.  Rows past a short segment's end are not fetched: the recompute
-// runs over whatever the area holds there, and the adjoint pass skips those
-// steps.
-template <typename IO, int BL, int L, int V, int KS, bool FAST>
-__device__ __forceinline__ void stateful_segment_items(const BwdArgs& ba, const LaneOff& lo,
-                                                       const Branches<BL, kKC<V>>& br, float alpha, int64_t bt0,
-                                                       int nk, Accum<BL, BL * kKC<V>>& acc, uint32_t* area,
-                                                       uint32_t* stage) {
+// e.g. ten compartments): pipelined over the lane's visits in visit_items'
+// order, but the next visit's X rows and checkpointed compartment state travel
+// by LDS DMA (dma_pieces) into the wave's LDS area, where they wait without
+// registers: the stash of a wide stateful neuron leaves none for rows in flight.
+// The small per-neuron rows (grad_spikes, grad_v_soma, the checkpointed H) ride
+// in registers, and grad_x leaves as whole pieces through the wave's `stage`
+// buffer (store_gx_staged).  The dendritic adjoint lam and dH cross chunk and
+// segment boundaries in reverse time within one neuron and restart at its last
+// chunk.  Rows past a short chunk's end are not fetched: the recompute runs over
+// whatever the area holds there, and the adjoint pass skips those steps.
+// MULTI: segments may hold several chunks.  Every run to a chunk then starts at
+// the segment's start (no slots: the plan's bsh keeps none), its state in
+// registers; with one chunk a segment (MULTI = false) none is carried.
+template <typename IO, int BL, int L, int V, int KS, bool FAST, bool MULTI>
+__device__ __forceinline__ void dma_visit_items(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
+                                                float alpha, int64_t bt0, int nk, Accum<BL, BL * kKC<V>>& acc,
+                                                uint32_t* area, uint32_t* stage) {
   constexpr int E = BL * kKC<V>;
   constexpr int W = E;               // fp32 rows: one dword per compartment
   constexpr int RD = kDmaDw<W>;      // LDS dwords per staged row
   static_assert(sizeof(IO) == 4 && !kSL<V> && !kCM<V>, "stateful wide fp32 lanes only");
   const ScanArgs& a = ba.s;
   const float beta_r = ba.detach ? 0.0f : a.beta;
-  const int T = int(a.T), K = a.K;
-  const int nseg = (T + K - 1) / K;
+  const int nseg = (int(a.T) + a.K - 1) / a.K;
   const Walk wk = make_walk<L, kCM<V>>(a, int64_t(a.ways) * a.M);
-  const int nvis = wk.nw * nk * nseg;
-  if (nvis <= 0) return;
-  struct Cursor {
-    int64_t n0, nx0;
-    int seg, w;
-  };
-  auto next = [&](Cursor& c) {
-    if (c.seg > 0) { --c.seg; return; }
-    c.seg = nseg - 1;
-    const bool last_w = ++c.w == wk.nw;
-    if (last_w) c.w = 0;
-    c.n0 += last_w ? wk.dn_item : wk.dn;
-    c.nx0 += last_w ? wk.dnx_item : wk.dnx;
-  };
-  Cursor ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0};
-  Cursor cp = ld;
+  int todo = wk.nw * nk;  // neurons whose last visit is still to be requested
+  if (todo <= 0) return;
+  VisitAt ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0, 0, 0, 0, 0, true, true};
+  enter_segment<KS>(a, ld);
+  VisitAt cp = ld;
   SegSmall<KS> cur;
-  issue_wide_segment<IO, BL, V, KS, FAST>(ba, lo, ld.n0, ld.nx0, ld.seg, area, cur);
-  next(ld);
+  issue_wide_visit<IO, BL, V, KS, FAST>(ba, lo, ld, area, cur);
+  todo -= next_visit<KS, false>(a, wk, nseg, ld) ? 1 : 0;
   BwdLane<IO, E> bl;
   bl.stage = stage;
   bl.dh_next = 0.0f;
   const uint32_t lane = __lane_id();
-  for (int i = 0; i < nvis; ++i) {
-    const int c0 = cp.seg * K;
-    const int len = min(K, T - c0);
-    if (cp.seg == nseg - 1) {  // the neuron's last segment: nothing after it
+  float v[E], h = 0.0f;  // state before the visit's chunk
+#pragma unroll
+  for (int j = 0; j < E; ++j) bl.lam[j] = v[j] = 0.0f;
+  bool s = false;
+  for (bool more = true; more;) {
+    const bool rev = !MULTI || cp.i == cp.j;
+    if (rev && cp.last && cp.seg == nseg - 1) {  // the neuron's last chunk: nothing after it
       bl.dh_next = 0.0f;
 #pragma unroll
       for (int j = 0; j < E; ++j) bl.lam[j] = 0.0f;
@@ -1861,16 +1812,20 @@ __device__ __forceinline__ void stateful_segment_items(const BwdArgs& ba, const 
     // the wave has completed
     __builtin_amdgcn_s_waitcnt(kWaitVmem);
     asm volatile("" ::: "memory");
-    float xin[KS][E], v0[E];
+    float xin[KS][E];
 #pragma unroll
     for (int k = 0; k < KS; ++k)
 #pragma unroll
       for (int j = 0; j < E; ++j) xin[k][j] = __uint_as_float(area[k * RD + lane * W + j]);
-    const bool from_ckpt = cp.seg > 0;
+    if (!MULTI || cp.first) {
+      const bool from_ckpt = cp.seg > 0;
 #pragma unroll
-    for (int j = 0; j < E; ++j) {  // (read unconditionally; the first segment starts from 0)
-      const float v = __uint_as_float(area[KS * RD + lane * W + j]);
-      v0[j] = from_ckpt ? v : 0.0f;
+      for (int j = 0; j < E; ++j) {  // (read unconditionally; the first segment starts from 0)
+        const float w = __uint_as_float(area[KS * RD + lane * W + j]);
+        v[j] = from_ckpt ? w : 0.0f;
+      }
+      h = cur.h0;
+      s = from_ckpt && h >= a.vth;
     }
     float gsv[KS], gvv[KS];
 #pragma unroll
@@ -1878,19 +1833,28 @@ __device__ __forceinline__ void stateful_segment_items(const BwdArgs& ba, const 
       gsv[k] = __uint_as_float(cur.gs[k]);
       gvv[k] = cur.gv[k];
     }
-    const float h0 = cur.h0;
     // the area is refilled only after these reads have completed
     __builtin_amdgcn_s_waitcnt(kWaitLds);
     asm volatile("" ::: "memory");
-    if (i + 1 < nvis) {
-      issue_wide_segment<IO, BL, V, KS, FAST>(ba, lo, ld.n0, ld.nx0, ld.seg, area, cur);
-      next(ld);
+    more = todo > 0;
+    if (more) {
+      issue_wide_visit<IO, BL, V, KS, FAST>(ba, lo, ld, area, cur);
+      todo -= next_visit<KS, false>(a, wk, nseg, ld) ? 1 : 0;
     }
-    Stash<BL, KS, V> st;
-    recompute_chunk<BL, L, V, KS, FAST>(a, br, alpha, v0, h0, from_ckpt && h0 >= a.vth, xin, st);
-    bl.gxbase = static_cast<IO*>(ba.gx) + cp.nx0;
-    reverse_chunk<IO, BL, L, V, KS, true, true>(ba, lo, br, alpha, beta_r, c0, st, gsv, gvv, bl, acc, len);
-    next(cp);
+    if (rev) {
+      Stash<BL, KS, V> st;
+      recompute_chunk<BL, L, V, KS, FAST>(a, br, alpha, v, h, s, xin, st);
+      IO* const gx = static_cast<IO*>(ba.gx) + cp.nx0 + int64_t(cp.c0) * (a.N * a.P);
+      reverse_chunk<IO, BL, L, V, KS, true, true>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cp.cs);
+    } else {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        if (k >= cp.cs) continue;
+        const float z = dendrite_step<BL, L, V, FAST>(v, xin[k], br, alpha);
+        soma_step(h, s, z, a.beta, a.vth);
+      }
+    }
+    next_visit<KS, false>(a, wk, nseg, cp);
   }
 }
 
@@ -2008,58 +1972,49 @@ __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& po
   }
 }
 
-// The backward of the lane's neurons: the short-sequence pipeline (T = KS),
-// the Stateless segment pipeline (K <= KS), or neuron by neuron.  ST: wide rows
-// staged (see load_pieces; lo.xw is the wave's stretch).
-template <typename IO, int BL, int L, int V, int KS, bool ST>
+// Which pipeline a backward kernel runs: every neuron one chunk of exactly KS
+// steps, one chunk of at most KS, visits over segments and chunks, or over
+// segments that are one chunk of KS steps each.
+enum BwdPath { kOneChunk = 0, kPartChunk = 1, kVisits = 2, kFullSegments = 3 };
+
+// The stateful dendrite's wide fp32 lanes move their rows by LDS DMA
+// (dma_visit_items).
+template <typename IO, int E, int V>
+constexpr bool kWideSF = kWideRow<IO, E, kCM<V>> && !kSL<V> && sizeof(IO) == 4;
+
+// The backward of the lane's neurons.  ST: wide rows staged (see load_pieces;
+// lo.xw is the wave's stretch).
+template <typename IO, int BL, int L, int V, int KS, int PATH, bool FAST, bool ST>
 __device__ __forceinline__ void bwd_run(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
                                         float alpha, int64_t bt0, int nk, Accum<BL, BL * kKC<V>>& acc,
-                                        uint32_t* stage) {
-  const ScanArgs& a = ba.s;
-  const int T = int(a.T);
-  // Without a gated-off branch in the wave (no mask, or a channel whose
-  // branches are all on) and without grad_v_soma, the pipelines run a copy
-  // without the per-step gate select and without grad_v_soma requests (bf16
-  // ImageNet-stem layer: 434 -> 396 VALU instructions per neuron; bf16 backward
-  // 1-2 % faster without the empty loads).  The vote is wave-uniform, so each
-  // wave runs one copy.
-  bool all_on = true;
-#pragma unroll
-  for (int j = 0; j < BL; ++j) all_on = all_on && br.on[j];
-  const bool fast = __all(all_on) && !ba.gv;
-  if constexpr (KS == 4) {
-    if (T == KS) {
-      if (fast) single_chunk_items<IO, BL, L, V, KS, true, ST>(ba, lo, br, alpha, bt0, nk, acc, stage);
-      else single_chunk_items<IO, BL, L, V, KS, false, ST>(ba, lo, br, alpha, bt0, nk, acc, stage);
-      return;
-    }
-  }
-  if constexpr (kSL<V>) {
-    if (a.K <= KS) {
-      if (fast) stateless_segment_items<IO, BL, L, V, KS, true, ST>(ba, lo, br, bt0, nk, acc, stage);
-      else stateless_segment_items<IO, BL, L, V, KS, false, ST>(ba, lo, br, bt0, nk, acc, stage);
-      return;
-    }
-  }
-  for (int i = 0; i < nk; ++i)
-    backward_neuron<IO, BL, L, V, KS, false>(ba, lo, bt0 + int64_t(i) * a.ways, br, alpha, acc, stage);
+                                        uint32_t* stage, float* bnd) {
+  if constexpr (PATH == kVisits || PATH == kFullSegments)
+    visit_items<IO, BL, L, V, KS, FAST, ST, (PATH == kFullSegments && !kWideSF<IO, BL * kKC<V>, V>)>(ba, lo, br, alpha, bt0, nk, acc, stage, bnd);
+  else
+    single_chunk_items<IO, BL, L, V, KS, FAST, ST, PATH == kPartChunk>(ba, lo, br, alpha, bt0, nk, acc, stage);
 }
 
-template <typename IO, int BL, int L, int V, int KS>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BL * kKC<V> * KS <= 8 ? 4 : (BL * kKC<V> * KS <= 16 ? 3 : 2)))) dendsn_bwd_kernel(BwdArgs ba) {
+// One pipeline a kernel, so that each has the registers it needs: with all of
+// them in one kernel, the longest-lived one set the occupancy of every other.
+// FAST (no mask and no grad_v_soma): no per-step gate select and no grad_v_soma
+// requests (bf16 ImageNet-stem layer: 434 -> 396 VALU instructions per neuron;
+// bf16 backward 1-2 % faster without the empty loads).
+template <int E, int KS, int PATH, bool FAST>
+constexpr int kBwdWaves = E * KS <= 8 ? 4 : (E * KS <= 16 || (FAST && PATH == kPartChunk && E <= 4) ? 3 : 2);
+
+template <typename IO, int BL, int L, int V, int KS, int PATH, bool FAST>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kBwdWaves<BL * kKC<V>, KS, PATH, FAST>))) dendsn_bwd_kernel(BwdArgs ba) {
   constexpr int E = BL * kKC<V>;
   constexpr int W = kRawW<IO, E, kCM<V>>;
   // Staged wide rows (see load_pieces) for the Stateless Dendrite's pipelines:
   // the stateful dendrite's stash of a wide lane left no room for the pieces
   // (its staged short-sequence copy spilled in the loop).
   constexpr bool kWide = kWideRow<IO, E, kCM<V>> && kSL<V>;
-  // The stateful dendrite's wide fp32 lanes move their rows by LDS DMA instead
-  // (stateful_segment_items).
-  constexpr bool kWideSF = kWideRow<IO, E, kCM<V>> && !kSL<V> && sizeof(IO) == 4;
+  constexpr bool kDma = kWideSF<IO, E, V>;
   if (ba.s.beta_p) ba.s.beta = ba.s.beta_p[0];  // learnable (PLIF) decay
   const ScanArgs& a = ba.s;
   const Pos pos = locate<L>(a);
-  const bool full = (kWide || kWideSF) && __all(pos.active);
+  const bool full = (kWide || kDma) && __all(pos.active);
   Accum<BL, E> acc;
 #pragma unroll
   for (int j = 0; j < BL; ++j) acc.k[j] = acc.z[j] = 0.0f;
@@ -2074,44 +2029,69 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(B
     LaneOff lo = lane_offsets<IO, E, kCM<V>>(a, pos);
     int64_t bt0;
     const int nk = items_of(a, pos, &bt0);
+    extern __shared__ float slots[];
+    float* bnd = slots;  // chunk-start states of segments longer than KS (see visit_items)
     bool done = false;
     if constexpr (kWide) {
       __shared__ uint32_t stage[kThreads / 64][64 * W];
       lo.xw = __builtin_amdgcn_readfirstlane(lo.x);
-      // staged where the loads are too: the two pipelines (the neuron-by-neuron
-      // path keeps lane loads and stores)
-      const bool pipelined = (KS == 4 && int(a.T) == KS) || a.K <= KS;
-      if (full && pipelined && stage_rows<IO>(a, lo.xw, bt0)) {
-        bwd_run<IO, BL, L, V, KS, true>(ba, lo, br, alpha, bt0, nk, acc, stage[threadIdx.x >> 6]);
+      if (full && stage_rows<IO>(a, lo.xw, bt0)) {
+        bwd_run<IO, BL, L, V, KS, PATH, FAST, true>(ba, lo, br, alpha, bt0, nk, acc, stage[threadIdx.x >> 6], bnd);
         done = true;
       }
     }
-    if constexpr (kWideSF) {
-      // one chunk per segment (with T = K = 4 every neuron is one segment:
-      // 221 -> 155 us on a T = 4, P = 10 stateful layer against the
-      // register-held short-sequence pipeline)
+    if constexpr (kDma) {
       __shared__ uint32_t area[kThreads / 64][(KS + 1) * kDmaDw<W>];   // rows in flight
       __shared__ uint32_t stage_sf[kThreads / 64][64 * W];              // grad_x leaving
+      // lane visits of long segments keep their slots in the area (5 E >= 4 (E + 1)
+      // dwords a lane); the DMA visits keep none, so a block has one or the other
+      bnd = reinterpret_cast<float*>(area);
       const uint32_t span = __builtin_amdgcn_readfirstlane(lo.x);
-      if (full && a.K <= KS && stage_rows<IO>(a, span, bt0)) {
+      if (full && a.K <= kDmaChunks * KS && stage_rows<IO>(a, span, bt0)) {
         lo.xw = span;
-        bool all_on = true;  // (as in bwd_run)
-#pragma unroll
-        for (int j = 0; j < BL; ++j) all_on = all_on && br.on[j];
-        if (__all(all_on) && !ba.gv)
-          stateful_segment_items<IO, BL, L, V, KS, true>(ba, lo, br, alpha, bt0, nk, acc, area[threadIdx.x >> 6],
-                                                          stage_sf[threadIdx.x >> 6]);
-        else
-          stateful_segment_items<IO, BL, L, V, KS, false>(ba, lo, br, alpha, bt0, nk, acc, area[threadIdx.x >> 6],
-                                                           stage_sf[threadIdx.x >> 6]);
+        dma_visit_items<IO, BL, L, V, KS, FAST, PATH == kVisits>(ba, lo, br, alpha, bt0, nk, acc,
+                                                                 area[threadIdx.x >> 6], stage_sf[threadIdx.x >> 6]);
         done = true;
       }
     }
-    if (!done) bwd_run<IO, BL, L, V, KS, false>(ba, lo, br, alpha, bt0, nk, acc, nullptr);
+    if (!done) bwd_run<IO, BL, L, V, KS, PATH, FAST, false>(ba, lo, br, alpha, bt0, nk, acc, nullptr, bnd);
   }
   if (pos.sub != 0) acc.b = 0.0f;  // the soma runs in every lane of a neuron: count it once
   // every thread of the block reaches this one call (it holds block barriers)
   reduce_partials<BL, E, L>(ba, pos, acc);
+}
+
+template <typename IO, int BL, int L, int V, int KS>
+hipError_t launch_bwd(const Plan& pl, const BwdArgs& ba, hipStream_t stream) {
+  const dim3 grid(static_cast<unsigned>(pl.ntiles * pl.G));
+  const bool fast = !ba.s.mask && !ba.gv;
+  const bool one = KS == 4 ? ba.s.T == KS : ba.s.T <= KS;
+#define DENDSN_BWD(PATH, FAST) \
+  { \
+    dendsn_bwd_kernel<IO, BL, L, V, KS, PATH, FAST><<<grid, dim3(kThreads), pl.lds, stream>>>(ba); \
+    return hipGetLastError(); \
+  }
+  if constexpr (kWideSF<IO, BL * kKC<V>, V>) {  // every segment one chunk, whole or not, or else
+    if (ba.s.K <= KS) {
+      if (fast) DENDSN_BWD(kFullSegments, true)
+      DENDSN_BWD(kFullSegments, false)
+    }
+  } else {
+    // (kFullSegments saves some of the visits' bookkeeping; it is compiled for the
+    // stateful dendrite in the compartments-innermost layout, ungated)
+    if constexpr (KS == 4) {
+      if (one && fast) DENDSN_BWD(kOneChunk, true)
+      if (one) DENDSN_BWD(kOneChunk, false)
+    } else {
+      if (one && fast) DENDSN_BWD(kPartChunk, true)
+      if (one) DENDSN_BWD(kPartChunk, false)
+    }
+    if constexpr (!kSL<V> && !kCM<V>)
+      if (fast && ba.s.K == KS && ba.s.T % KS == 0) DENDSN_BWD(kFullSegments, true)
+  }
+  if (fast) DENDSN_BWD(kVisits, true)
+  DENDSN_BWD(kVisits, false)
+#undef DENDSN_BWD
 }
 
 // Fixed-order float64 sum of the partials into the parameter gradients;

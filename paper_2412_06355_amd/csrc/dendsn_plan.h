@@ -8,6 +8,8 @@ namespace dendsn {
 
 constexpr int kThreads = 256;  // 4 wave64s per block
 
+constexpr bool long_stash(int BL, int L, int KC, bool cm) { return BL * KC == 4 && (L <= 4 || (KC == 1 && !cm)); }
+
 // The backward translation units are compiled once per surrogate derivative
 // (-DDENDSN_SG=0: atan, 1: sigmoid), which is bit 5 of the kernel variant V; their
 // launchers carry the suffix _sg0 / _sg1.
@@ -40,7 +42,9 @@ struct Plan {
   int32_t bpg;    // batch items per group
   int32_t KS;     // backward stash capacity in steps (compile-time in the kernel)
   int32_t nck;    // interior checkpoints, ceil(T / K) - 1
-  int32_t lds;    // dynamic LDS bytes per block, reserved only to cap blocks per CU
+  int32_t lds;    // dynamic LDS bytes per block: chunk-start slots of the backward, or room
+                  // reserved only to cap blocks per CU
+  int32_t bsh;    // the slots keep every (1 << bsh)-th chunk start of a segment
   int32_t nw;     // positions per lane and batch item in spatial tiles (1, 2 or 4)
   int32_t xk;     // XCD runs: consecutive tiles per XCD turn (1: plain round-robin)
 };
@@ -60,6 +64,7 @@ struct ScanArgs {
   float rP;             // 1 / P (residual dendrite)
   int32_t mode, ways, pb, tpc, cpt, bpg;
   int32_t nw;           // spatial tiles: a lane takes positions p, p + 64 / L, ... (nw of them)
+  int32_t bsh;          // backward: every (1 << bsh)-th chunk start of a segment is kept
   int32_t xk;           // runs of xk consecutive blocks share an XCD (see locate)
   int32_t stg;          // 1: a sample's slice of X is a multiple of 16 bytes (wide rows may be staged)
   int64_t ntiles;
@@ -107,6 +112,10 @@ struct FinArgs {
   int32_t B, P, KC, wide, stateful;
 };
 
+// Backward of the wide stateful fp32 lanes: segments of up to this many chunks
+// keep their LDS DMA pipeline (without chunk-start slots).
+constexpr int kDmaChunks = 4;
+
 constexpr int kNarrowSlots = 16;  // up to this many partial slots: one thread per output
 
 // Runtime kernel variant v = psi | residual << 1 | stateless << 2, as the host
@@ -120,8 +129,10 @@ constexpr int variant_bits(int v) { return (v & 3) | ((v & 4) << 4); }
 // of the neuron over lanes (pairwise in a lane, then the DPP butterfly), so
 // the forward and the backward may split a neuron differently and still agree
 // bit for bit.
-// Backward stash capacities: 4 steps for every mapping, and 8 steps too when a
-// lane holds at most 4 branches.
+// Backward stash capacities: 4 steps for every mapping, and 8 steps too
+// (long_stash) where a lane holds exactly 4 compartments, over at most 4 lanes in
+// the channel-major layout and with several compartments per branch (wider or
+// narrower lanes run long sequences in chunks of 4 steps).
 #define DENDSN_FAST_F32(X) X(4, 1) X(4, 2) X(4, 4) X(4, 8) X(4, 16)
 // The fp32 forward also holds 8 branches per lane over two lanes (16 branches).
 #define DENDSN_FAST_F32_FWD(X) DENDSN_FAST_F32(X) X(8, 2)
@@ -129,7 +140,6 @@ constexpr int variant_bits(int v) { return (v & 3) | ((v & 4) << 4); }
 // The bf16 backward also holds 4 branches per lane (8 bytes) up to 64 branches.
 #define DENDSN_FAST_BF16_BWD(X) DENDSN_FAST_BF16(X) X(4, 2) X(4, 4) X(4, 8) X(4, 16)
 #define DENDSN_GENERIC(X) X(1, 1) X(2, 1) X(3, 1) X(5, 1) X(6, 1) X(7, 1) X(5, 2) X(6, 2) X(7, 2)
-#define DENDSN_GENERIC_KS 4
 
 // Compiled (BL, L, KC) mappings with KC = 2 or 4 compartments per branch (stash
 // capacity 4).  Fast ones put 16 bytes of compartments in a lane (BL KC = 4

@@ -233,8 +233,8 @@ def test_stateful_wide_rows_segment_pipeline(gpu_device, shape, variant):
 
 @pytest.mark.parametrize("B,k,io", [(5, 2, "f32"), (7, 2, "f32"), (5, 2, "bf16")])
 def test_wide_rows_checkpoint_interval_is_bit_invariant(gpu_device, B, k, io):
-    """K = 2 and 4 take the stateful segment pipeline (fp32), K = 12 the
-    neuron-by-neuron path: spikes and every gradient agree bit for bit."""
+    """K = 2 and 4 take the stateful segment pipeline (fp32), K = 12 its visits
+    of several chunks a segment: spikes and every gradient agree bit for bit."""
     import torch
 
     base = cfg(T=12, batch=2, C=4, S=64, B=B, comps_per_branch=k, io=io, beta=0.8, ckpt_every=4)
@@ -429,6 +429,46 @@ def test_checkpoint_interval_is_bit_invariant(gpu_device):
         assert torch.equal(o["spikes"], ref["spikes"])
         assert torch.equal(o["v_soma"], ref["v_soma"])
         assert torch.equal(_bits(o["grads"]["grad_x"]), _bits(ref["grads"]["grad_x"]))
+
+
+# Segments longer than the backward's chunks (8 steps where a lane holds four
+# compartments, else 4): T, batch, C, S, B, k, io, layout.
+LONG_SEGMENTS = [
+    (7, 3, 5, 49, 2, 2, "bf16", "channel_major"),   # one chunk of fewer than 8 steps
+    (9, 2, 4, 64, 4, 1, "f32", "npb"),              # two chunks, the first of one step
+    (33, 5, 70, 1, 8, 1, "bf16", "npb"),            # chunks with kept starts, fully connected
+    (100, 1, 2, 64, 4, 1, "f32", "npb"),            # more starts than LDS slots: every second kept
+    (70, 1, 3, 30, 4, 2, "bf16", "npb"),            # 18 chunks of 4, every fourth start kept
+    (14, 2, 4, 64, 5, 2, "f32", "npb"),             # wide stateful rows: DMA visits of four chunks
+    (14, 2, 3, 50, 5, 2, "f32", "npb"),             # the same with ragged waves (lane visits)
+    (30, 2, 3, 64, 3, 2, "f32", "npb"),             # wide rows, more chunks than the DMA visits take
+    (11, 2, 3, 36, 3, 1, "f32", "channel_major"),   # a narrow lane, chunks of 4
+]
+
+
+@pytest.mark.parametrize("shape", LONG_SEGMENTS, ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}".format(*s))
+@pytest.mark.parametrize("variant", ["stateful", "stateful-mask-gv", "stateless-res"])
+def test_long_segments_match_checkpointed_ones(gpu_device, shape, variant):
+    """Without checkpoints a sequence is one segment of several chunks: the same
+    spikes and grad_x, bit for bit, as with checkpoints every 4 steps and (two
+    chunks of unequal length a segment) every 7, and the oracle's values."""
+    import torch
+
+    T, batch, C, S, B, k, io, layout = shape
+    base = cfg(T=T, batch=batch, C=C, S=S, B=B, comps_per_branch=k, io=io, layout=layout, beta=0.6,
+               stateful="stateless" not in variant, residual="res" in variant, sg="atan")
+    case = make_case(base, seed=zlib.crc32(repr((shape, variant)).encode()) % 10000, alpha=0.6,
+                     mask_rho=0.6 if "mask" in variant else None, with_gv="gv" in variant,
+                     name=f"long-seg/{shape}/{variant}")
+    d = to_device(case, gpu_device)
+    outs = []
+    for K in (4, 7, 0):
+        case.cfg = base.with_(ckpt_every=K)
+        outs.append(run_gpu(case, gpu_device, dev=d))
+    for o in outs[:2]:
+        assert torch.equal(_bits(o["raw"]["spikes"]), _bits(outs[2]["raw"]["spikes"]))
+        assert torch.equal(_bits(o["raw"]["grads"]["grad_x"]), _bits(outs[2]["raw"]["grads"]["grad_x"]))
+    compare(case, outs[2])
 
 
 @pytest.mark.parametrize("shape", ["generic-kc2-S40", "fast-kc1-fc", "bf16-kc2-S300"])
