@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -272,7 +273,13 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   const int L = p.L;
   const int esz = c->io == DENDSN_IO_BF16 ? 2 : 4;
   p.nw = 1;
-  if (c->S >= kThreads / L) {
+  // A tile that holds one channel's whole map (pb / 2 < S < pb) is a spatial tile in
+  // the backward: its block reduction is parallel over the positions, where a kSeg
+  // tile's thread adds its channel's S positions one by one (14x14 maps, 256
+  // channels, 8 samples, B = 4: backward 82.5 -> 18.2 us with the groups below).
+  // Smaller maps, two or more channels a tile, stay kSeg: 11x11 maps of ten
+  // compartments, T = 10, 74 us against 88, B = 8 on 7x7 51 against 57-77.
+  if (c->S >= kThreads / L || (bwd && 2 * c->S > kThreads / L)) {
     p.mode = kSpatial; p.ways = 1; p.pb = kThreads / L;
     // A lane may take nw positions per batch item, so a wave reads and writes
     // nw x 64 / L adjacent positions per row (fewer, longer-lived waves).
@@ -340,6 +347,34 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   const int64_t max_g = ceil_div(c->batch, p.ways);
   if (G > max_g) G = max_g;
   if (bwd && p.mode != kSpatial && G > 8) G = 8;  // bounds the per-group partials
+  // Small layers (GPU time per launch, MI355X).  Fully connected tiles and the
+  // backward's kSeg tiles: at least two blocks per CU, down to one batch item a
+  // wave (four branches, 128 channels, 512 samples: forward 4.9 -> 3.5 us, backward
+  // 21.4 -> 9.6; five branches of two, 700 channels, 300 samples, T = 10:
+  // 144.8 -> 82.4; 4x4 maps, 256 channels, 128 samples, bf16: 57.7 -> 29.7).  Past
+  // that the per-block reduction and the partials cost more than they hide (500
+  // channels: 64 groups 10.9, 128 groups 15.6), and a layer that fills the chip
+  // already keeps its groups.  The partials stay below 15 MiB (fewer than 1024
+  // blocks of at most 256 / (L S) channels).
+  const bool fill = p.mode == kFC || (bwd && p.mode == kSeg);
+  if (fill) G = std::max(G, ceil_div(512, p.ntiles));
+  // The forward over kSeg tiles: two items a wave once that leaves 1024 blocks
+  // (14x14, 256 channels, 8 samples: 8.7 -> 7.3 us; 12x12, T = 8, bf16: 16.1 -> 13.4;
+  // four items 13.1 and 7.2, but 30 % slower on 4x4 maps).
+  if (!bwd && p.mode == kSeg) G = std::min(G, std::max(ceil_div(1024, p.ntiles), ceil_div(c->batch, 2)));
+  // The backward over spatial tiles of one position per lane: four items a block
+  // once that leaves 512 blocks (28x28, T = 6, bf16: 50.6 -> 40.8 us; 14x14, 32
+  // samples: 93 -> 60; 16x16, 64 samples: 27.4 -> 20.5; 32x32, ten compartments:
+  // 65.3 -> 59.3).  With several positions per lane fewer groups gained and lost
+  // (32x32, 64 channels, 16 samples: 34.3 us with 16 groups, 36.4 with 4): unchanged.
+  // Fewer items where four would be more than 24 steps of one lane's fp32 sums (ten
+  // steps, ten compartments, 32x32: no faster with four than with two, and the error
+  // of g_beta twice as large).
+  if (bwd && p.mode == kSpatial && p.nw == 1) {
+    const int64_t items = std::min<int64_t>(4, std::max<int64_t>(1, 24 / c->T));
+    G = std::min(G, std::max(ceil_div(512, p.ntiles), ceil_div(c->batch, items)));
+  }
+  G = std::min(G, max_g);
   if (c->batch_groups > 0) G = c->batch_groups < c->batch ? c->batch_groups : c->batch;
   p.bpg = int32_t(ceil_div(c->batch, G));
   p.G = int32_t(ceil_div(c->batch, p.bpg));

@@ -1236,12 +1236,12 @@ __global__ void __launch_bounds__(kThreads) dendsn_fwd_kernel(FwdArgs fa) {
 
 // ---------------------------------------------------------------------------
 // Backward kernel.  For each neuron, the segments between checkpoints are
-// visited from last to first.  A segment is cut into whole chunks of
-// compile-time length (KS, then powers of two for the remainder); a chunk
-// re-runs the forward from the segment's checkpoint up to its first step (only
-// chunks after the first need that), recomputes its own steps while stashing
-// the dendritic state and H in registers, then runs the adjoint recurrences
-// backwards through them.
+// visited from last to first.  A segment is cut into chunks of compile-time
+// length KS (the first may be shorter), each a visit of the memory pipeline
+// (BwdPath): a chunk starts from the checkpoint, or from a state of the same
+// segment kept in LDS, recomputes its own steps while stashing the dendritic
+// state and H in registers, then runs the adjoint recurrences backwards through
+// them.
 // ---------------------------------------------------------------------------
 template <int BL, int E>
 struct Accum {

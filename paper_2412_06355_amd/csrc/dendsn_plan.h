@@ -21,9 +21,9 @@ constexpr bool long_stash(int BL, int L, int KC, bool cm) { return BL * KC == 4 
 // Tiles never straddle a channel unless they hold whole channels, so a block's
 // parameter-gradient partials belong to a known set of channels.
 enum TileMode : int32_t {
-  kSpatial = 0,  // S >= positions per block: a tile is pb positions of ONE channel
+  kSpatial = 0,  // large S: a tile is pb positions of ONE channel (the last one fewer)
   kFC = 1,       // S == 1: a tile is pb channels; the 4 waves split the batch items
-  kSeg = 2,      // 1 < S < pb: a tile is cpt whole channels of S positions
+  kSeg = 2,      // small S > 1: a tile is cpt whole channels of S positions
 };
 
 struct Plan {

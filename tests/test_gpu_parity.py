@@ -619,6 +619,40 @@ def test_batch_grouping_changes_nothing_but_rounding(gpu_device):
     compare(case, b)
 
 
+# --- small layers: tiles of one channel's whole map (256 / L / 2 < S < 256 / L) and
+# the batch groups that fill the chip (ragged last groups, one item a wave) ---
+SMALL_LAYERS = [
+    # T, batch, C, S, B, k, io, layout
+    (4, 9, 3, 129, 4, 1, "f32", "npb"),             # the smallest map with a tile of its own, one lane
+    (4, 5, 3, 255, 2, 2, "bf16", "channel_major"),  # the largest below a whole tile
+    (4, 6, 5, 128, 2, 2, "f32", "npb"),             # two channels a tile still
+    (5, 7, 3, 65, 8, 1, "f32", "npb"),              # two lanes per neuron
+    (4, 6, 2, 200, 5, 2, "f32", "npb"),             # wide stateful rows, an inactive tail of the last wave
+    (4, 300, 70, 1, 2, 2, "f32", "npb"),            # fully connected: one item a wave, two tiles
+    (6, 37, 600, 1, 16, 1, "bf16", "npb"),          # fully connected over several lanes, ragged groups
+    (4, 75, 9, 16, 4, 1, "f32", "npb"),             # whole channels a tile, one tile, one item a group
+]
+
+
+@pytest.mark.parametrize("shape", SMALL_LAYERS, ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}".format(*s))
+@pytest.mark.parametrize("variant", ["stateful-mask", "stateless-res"])
+def test_small_layers_tiles_and_groups(gpu_device, shape, variant):
+    import torch
+
+    T, batch, C, S, B, k, io, layout = shape
+    c = cfg(T=T, batch=batch, C=C, S=S, B=B, comps_per_branch=k, io=io, layout=layout, beta=0.6,
+            stateful="stateless" not in variant, residual="res" in variant)
+    case = make_case(c, seed=zlib.crc32(repr((shape, variant)).encode()) % 10000, alpha=0.6,
+                     mask_rho=0.6 if "mask" in variant else None, name=f"small/{shape}/{variant}")
+    d = to_device(case, gpu_device)
+    a = run_gpu(case, gpu_device, dev=d)
+    compare(case, a)
+    case.cfg = c.with_(batch_groups=2)
+    b = run_gpu(case, gpu_device, dev=d)
+    assert torch.equal(a["raw"]["spikes"], b["raw"]["spikes"])
+    assert torch.equal(_bits(a["raw"]["grads"]["grad_x"]), _bits(b["raw"]["grads"]["grad_x"]))
+
+
 def test_forward_without_checkpoints_for_inference(gpu_device):
     import torch
 
