@@ -279,7 +279,12 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // channels, 8 samples, B = 4: backward 82.5 -> 18.2 us with the groups below).
   // Smaller maps, two or more channels a tile, stay kSeg: 11x11 maps of ten
   // compartments, T = 10, 74 us against 88, B = 8 on 7x7 51 against 57-77.
-  if (c->S >= kThreads / L || (bwd && 2 * c->S > kThreads / L)) {
+  // One lane per neuron with rows of at most 16 bytes takes one from 7/16 of a tile on
+  // (11x11, 128 channels, 64 samples, two branches of two: backward 53.7 -> 48.1 us
+  // channel-major, 45.2 -> 43.4 otherwise); with idle waves in half the block, smaller
+  // maps lose what the reduction gains.
+  const bool one_map = 2 * c->S > kThreads / L || (L == 1 && p.BL * p.KC * esz <= 16 && 16 * c->S >= 7 * kThreads);
+  if (c->S >= kThreads / L || (bwd && one_map)) {
     p.mode = kSpatial; p.ways = 1; p.pb = kThreads / L;
     // A lane may take nw positions per batch item, so a wave reads and writes
     // nw x 64 / L adjacent positions per row (fewer, longer-lived waves).

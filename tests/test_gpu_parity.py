@@ -625,7 +625,8 @@ SMALL_LAYERS = [
     # T, batch, C, S, B, k, io, layout
     (4, 9, 3, 129, 4, 1, "f32", "npb"),             # the smallest map with a tile of its own, one lane
     (4, 5, 3, 255, 2, 2, "bf16", "channel_major"),  # the largest below a whole tile
-    (4, 6, 5, 128, 2, 2, "f32", "npb"),             # two channels a tile still
+    (4, 6, 5, 112, 2, 2, "f32", "npb"),             # 7/16 of a tile: a tile of its own in the backward
+    (4, 6, 5, 111, 2, 2, "f32", "npb"),             # two channels a tile still
     (5, 7, 3, 65, 8, 1, "f32", "npb"),              # two lanes per neuron
     (4, 6, 2, 200, 5, 2, "f32", "npb"),             # wide stateful rows, an inactive tail of the last wave
     (4, 300, 70, 1, 2, 2, "f32", "npb"),            # fully connected: one item a wave, two tiles
