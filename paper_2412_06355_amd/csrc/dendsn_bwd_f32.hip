@@ -25,19 +25,20 @@ static hipError_t launch_bwd_v(const Plan& pl, const BwdArgs& ba, int v, hipStre
 }
 
 hipError_t DENDSN_SG_NAME(launch_bwd_f32)(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream) {
-#define DENDSN_FAST_CASE(BL_, L_)                                                   \
-  if (pl.BL == BL_ && pl.L == L_ && pl.fast) {                                      \
+#define DENDSN_CASE(FAST_, BL_, L_)                                                 \
+  if (bool(pl.fast) == FAST_ && pl.BL == BL_ && pl.L == L_) {                       \
     if (pl.KS == 4) return launch_bwd_v<BL_, L_, 4>(pl, ba, v, stream); \
     if constexpr (long_stash(BL_, L_, 1, false))                                                         \
       if (pl.KS == 8) return launch_bwd_v<BL_, L_, 8>(pl, ba, v, stream); \
     return hipErrorInvalidValue;                                                    \
   }
-#define DENDSN_GENERIC_CASE(BL_, L_)                                                \
-  if (pl.BL == BL_ && pl.L == L_ && !pl.fast && pl.KS == 4) return launch_bwd_v<BL_, L_, 4>(pl, ba, v, stream);
+#define DENDSN_FAST_CASE(BL_, L_) DENDSN_CASE(true, BL_, L_)
+#define DENDSN_GENERIC_CASE(BL_, L_) DENDSN_CASE(false, BL_, L_)
   DENDSN_FAST_F32(DENDSN_FAST_CASE)
   DENDSN_GENERIC(DENDSN_GENERIC_CASE)
 #undef DENDSN_FAST_CASE
 #undef DENDSN_GENERIC_CASE
+#undef DENDSN_CASE
   return hipErrorInvalidValue;
 }
 

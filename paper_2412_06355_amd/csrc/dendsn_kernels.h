@@ -1273,8 +1273,9 @@ struct ChunkRaw {
 // PART: only the first cs rows exist (cs is wave-uniform); the others are read
 // through buffers of no bytes, so they cost no memory traffic and the number of
 // requests, which the waits are counted by, stays the same.  GV = false:
-// grad_v_soma is known absent, nothing is requested (else absent rows are a
-// buffer of gvbytes = 0 bytes: every load returns 0).  rev = false: X alone.
+// grad_v_soma is known absent; else gvbytes = 0 says that it is (one uniform
+// branch: requests through empty buffers cost a masked bf16 layer of twelve steps,
+// K = 4, 5 %).  rev = false: X alone.
 // PAIRED: grad_spikes row by row with X (one-chunk neurons of four steps: 0.5-1 %
 // faster); else behind all X rows, which the recompute waits for first (bf16
 // ten-step layer 826 -> 752 us, 64 steps with K = 8: 236 -> 227 us).
@@ -1302,12 +1303,16 @@ __device__ __forceinline__ void load_chunk_raw(const ScanArgs& a, const LaneOff&
 #pragma unroll
     for (int k = 0; k < CS; ++k) load_gs(k);
   }
+  if (GV && gvbytes) {
 #pragma unroll
-  for (int k = 0; k < CS; ++k) {
-    in.gv[k] = GV ? __uint_as_float(
-                        __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(gv, bytes(k, rev, gvbytes)), lo.v, 0, kAuxNT))
-                  : 0.0f;
-    gv += a.N;
+    for (int k = 0; k < CS; ++k) {
+      in.gv[k] = __uint_as_float(
+          __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(gv, bytes(k, rev, gvbytes)), lo.v, 0, kAuxNT));
+      gv += a.N;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < CS; ++k) in.gv[k] = 0.0f;
   }
 }
 
@@ -1511,18 +1516,19 @@ __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const Lane
 }
 
 // Every other sequence: segments of K steps between checkpoints, visited from
-// last to first, each cut into chunks of KS steps with the remainder first.
-// Every chunk is one visit of the memory pipeline: the next visit's rows are
-// requested before this visit computes, so they stream in meanwhile.  A segment
-// of one chunk (K <= KS) is visited once.  A longer one is first run forward up
-// to its last chunk (advance visits, X rows only), each chunk's starting state
-// going to the lane's LDS slots; then every chunk, last to first, is recomputed
-// from its slot and reversed.  So X is read at most twice, whatever T / KS
-// (before, each chunk re-ran the forward from the segment's start with no load
-// in flight: T^2 / KS reads).  Where the slots do not hold every chunk's start,
-// they hold every (1 << bsh)-th one, and a chunk between two advances from the
-// slot below it.  Rows past a short chunk's end go through buffers of no bytes
-// and are skipped by the arithmetic.
+// last to first.  A segment of at most KS steps is one visit of the memory
+// pipeline (SEG); a longer one is cut into chunks of KS steps with the remainder
+// first.  The next visit's rows are requested before this visit computes, so they
+// stream in meanwhile.  A segment of several chunks is first run forward up to its
+// last chunk (advance visits, X rows only), each chunk's starting state going to
+// the lane's LDS slots; then every chunk, last to first, is recomputed from its
+// slot and reversed.  With every start kept (bsh = 0) X is read at most twice;
+// where the slots hold every (1 << bsh)-th start, a chunk between two advances
+// again from the slot below it, about 1 + (2^bsh + 1) / 2 reads in all, and as
+// bsh grows with T / KS, very long segments without checkpoints stay quadratic in
+// T.  (Re-running each chunk from the segment's start with no load in flight,
+// T = 64 bf16: 3070 us against 594.)  Rows past a short chunk's end go through
+// buffers of no bytes and are skipped by the adjoint pass.
 template <typename IO, int E, int CS, bool CM, bool ST, bool SL>
 struct VisitRaw {
   ChunkRaw<IO, E, CS, CM, ST> in;
@@ -1539,7 +1545,14 @@ struct VisitAt {
   int c0, cs;   // first step and length of chunk i
   bool first;   // the visit starts its run (its state comes from a checkpoint or a slot)
   bool last;    // the segment's last chunk is being reversed
+  bool pre;     // the run starts at chunk 1: the visit itself steps through chunk 0
 };
+
+// Two-chunk segments whose first chunk is this short are not given an advance
+// visit: the visit of the second chunk reads those rows itself (one more visit of
+// KS requested rows cost more than the wait: five steps of bf16, 784 positions,
+// 128 channels, B = 1 55.1 against 98.9 us, ten compartments 288 against 389).
+constexpr int kPreSteps = 2;
 
 // Chunk i of segment seg: i = 0 holds the remainder.
 template <int KS>
@@ -1549,19 +1562,26 @@ __device__ __forceinline__ void place_chunk(const ScanArgs& a, VisitAt& c) {
   c.c0 = c.i > 0 ? t0 + rem + (c.i - 1) * KS : t0;
   c.cs = c.i > 0 ? KS : rem;
 }
-// The start of a segment's first run, to its last chunk.
-template <int KS>
+// The start of a segment's first run, to its last chunk.  PRE: see kPreSteps.
+template <int KS, bool SEG, bool PRE>
 __device__ __forceinline__ void enter_segment(const ScanArgs& a, VisitAt& c) {
-  c.j = (min(a.K, int(a.T) - c.seg * a.K) - 1) / KS;
-  c.i = 0;
-  c.first = c.last = true;
-  place_chunk<KS>(a, c);
+  if constexpr (SEG) {
+    c.c0 = c.seg * a.K;
+    c.cs = min(a.K, int(a.T) - c.c0);
+  } else {
+    const int len = min(a.K, int(a.T) - c.seg * a.K);
+    c.j = (len - 1) / KS;
+    c.pre = PRE && c.j == 1 && len - KS <= kPreSteps;
+    c.i = c.pre ? 1 : 0;
+    c.first = c.last = true;
+    place_chunk<KS>(a, c);
+  }
 }
-// The next visit; true where it is another neuron's first.  FULL: every segment
-// is one chunk of KS steps.
-template <int KS, bool FULL>
+// The next visit; true where it is another neuron's first.  SEG: every segment is
+// one chunk.
+template <int KS, bool SEG, bool PRE = true>
 __device__ __forceinline__ bool next_visit(const ScanArgs& a, const Walk& wk, int nseg, VisitAt& c) {
-  if (!FULL && c.j > 0) {
+  if (!SEG && c.j > 0) {
     if (c.i < c.j) {  // on towards chunk j
       ++c.i;
       c.first = false;
@@ -1571,7 +1591,7 @@ __device__ __forceinline__ bool next_visit(const ScanArgs& a, const Walk& wk, in
     --c.j;  // the chunk below, from the slot at or below it
     c.i = (c.j >> a.bsh) << a.bsh;
     c.first = true;
-    c.last = false;
+    c.last = c.pre = false;
     place_chunk<KS>(a, c);
     return false;
   }
@@ -1584,8 +1604,7 @@ __device__ __forceinline__ bool next_visit(const ScanArgs& a, const Walk& wk, in
     c.nx0 += last_w ? wk.dnx_item : wk.dnx;
   }
   --c.seg;
-  if constexpr (FULL) c.c0 = c.seg * KS;
-  else enter_segment<KS>(a, c);
+  enter_segment<KS, SEG, PRE>(a, c);
   return neuron;
 }
 
@@ -1595,36 +1614,49 @@ __device__ __forceinline__ bool next_visit(const ScanArgs& a, const Walk& wk, in
 template <typename IO, int V>
 constexpr bool kEarlyVisit = sizeof(IO) == 2 || kSL<V>;
 
+// Whether the recompute skips the padding steps of a short chunk (a branch a
+// step) or runs them too, with the steps of a chunk scheduled together.  Running
+// them is faster (Stateless bf16, twelve steps, K = 4: 10-15 %; a masked layer 5 %)
+// as long as the registers last: wide lanes spilled (fourteen compartments fp32
+// 380 -> 720 us, ten stateful bf16 345 -> 394), and so did the multi-chunk visits
+// of the stateful dendrite (24 steps bf16: 141 -> 155 us) and the channel-major
+// eight-step ones with the Mexican hat (183 -> 202).
+template <int E, int V, int KS, bool SEG>
+constexpr bool kSkipPad = E >= 12 || (SEG ? E >= 10 && kMH<V> && !kSL<V> : !kSL<V> || (kCM<V> && KS == 8 && kMH<V>));
+
 // more = false: past the last visit, everything through buffers of no bytes
-// (early requests are unconditional, see the waits below).
-template <typename IO, int BL, int L, int V, int KS, bool GV, bool ST, bool FULL>
+// (early requests are unconditional, see the waits below).  EXACT: a segment is
+// KS steps.
+template <typename IO, int BL, int L, int V, int KS, bool GV, bool ST, bool SEG, bool EXACT>
 __device__ __forceinline__ void load_visit(const BwdArgs& ba, const LaneOff& lo, const VisitAt& c, bool more,
                                            VisitRaw<IO, BL * kKC<V>, KS, kCM<V>, ST, kSL<V>>& r) {
   constexpr int E = BL * kKC<V>;
   const ScanArgs& a = ba.s;
-  // The state checkpointed after step c0 - 1, where a run starts from it (else a
+  // The state checkpointed before the segment, where a run starts from it (else a
   // buffer of no bytes: zeros, as for the first segment).
-  const bool ck = more && c.seg > 0 && (FULL || c.i == 0);
+  const bool ck = more && c.seg > 0 && (SEG || c.i == 0 || c.pre);
   const int64_t at_ck = ck ? int64_t(c.seg - 1) * a.N + c.n0 : 0;
   const uint32_t nb = uniform_u32(ck ? 0xFFFFFFFFu : 0u);
   if constexpr (!kSL<V>)
     bload_vec<E>(make_rsrc(uniform_ptr(ba.ckpt + at_ck * a.P), nb), lo.c, r.v0, static_cast<const float*>(nullptr));
   r.h0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(uniform_ptr(ba.ckh + at_ck), nb), lo.v, 0, kAuxNT));
   const int64_t row = int64_t(c.c0) * a.N;
-  load_chunk_raw<IO, E, KS, kCM<V>, GV, ST, !(FULL && !kEarlyVisit<IO, V>)>(a, lo, static_cast<const IO*>(a.x) + c.nx0 + row * a.P,
+  load_chunk_raw<IO, E, KS, kCM<V>, GV, ST, true>(a, lo, static_cast<const IO*>(a.x) + c.nx0 + row * a.P,
                                                   static_cast<const IO*>(ba.gspk) + c.n0 + row,
-                                                  ba.gvz + c.n0 + row, ba.gvn, r.in, !more ? 0 : (FULL ? KS : c.cs),
-                                                  FULL || c.i == c.j);
+                                                  ba.gvz + c.n0 + row, ba.gvn, r.in, !more ? 0 : (EXACT ? KS : c.cs),
+                                                  SEG || c.i == c.j);
 }
 
-template <typename IO, int BL, int L, int V, int KS, bool FAST, bool ST, bool FULL>
+template <typename IO, int BL, int L, int V, int KS, bool FAST, bool ST, bool SEG, bool EXACT>
 __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
                                             float alpha, int64_t bt0, int nk, Accum<BL, BL * kKC<V>>& acc,
                                             uint32_t* stage, float* bnd) {
+  static_assert(SEG || !EXACT, "exact segments are one chunk each");
   constexpr int E = BL * kKC<V>;
   constexpr int W = kRawW<IO, E, kCM<V>>;
   constexpr int SE = kSL<V> ? 0 : E;  // compartment states kept per slot
   constexpr bool kEarly = kEarlyVisit<IO, V>;
+  constexpr bool kSkip = !EXACT && kSkipPad<E, V, KS, SEG>;
   using Raw = VisitRaw<IO, E, KS, kCM<V>, ST, kSL<V>>;
   const ScanArgs& a = ba.s;
   const float beta_r = ba.detach ? 0.0f : a.beta;
@@ -1634,12 +1666,12 @@ __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo
   if (todo <= 0) return;
   const int bsh = a.bsh;
   bnd += threadIdx.x;
-  VisitAt ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0, 0, 0, 0, 0, true, true};
-  enter_segment<KS>(a, ld);
+  VisitAt ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0, 0, 0, 0, 0, true, true, false};
+  enter_segment<KS, SEG, true>(a, ld);
   VisitAt cp = ld;
   Raw cur;
-  load_visit<IO, BL, L, V, KS, !FAST, ST, FULL>(ba, lo, ld, true, cur);
-  todo -= next_visit<KS, FULL>(a, wk, nseg, ld) ? 1 : 0;
+  load_visit<IO, BL, L, V, KS, !FAST, ST, SEG, EXACT>(ba, lo, ld, true, cur);
+  todo -= next_visit<KS, SEG>(a, wk, nseg, ld) ? 1 : 0;
   // Every later wait is then counted from loads issued inside the loop, which
   // are unconditional (past the last visit, rows of no bytes).
   __builtin_amdgcn_s_waitcnt(kWaitVmem);
@@ -1651,8 +1683,8 @@ __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo
   for (int j = 0; j < E; ++j) bl.lam[j] = v[j] = 0.0f;
   bool s = false;
   auto visit = [&](const Raw& in, bool more, Raw& nxt) {
-    if (FULL || cp.first) {
-      if (FULL || cp.i == 0) {
+    if (SEG || cp.first) {
+      if (SEG || cp.i == 0 || cp.pre) {
 #pragma unroll
         for (int j = 0; j < E; ++j) v[j] = kSL<V> ? 0.0f : in.v0[kSL<V> ? 0 : j];
         h = in.h0;
@@ -1665,6 +1697,18 @@ __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo
         s = h >= a.vth;
       }
     }
+    if (!SEG && cp.pre) {  // chunk 0, read here
+      const IO* xr = static_cast<const IO*>(a.x) + cp.nx0 + int64_t(cp.seg) * a.K * (a.N * a.P);
+#pragma unroll 1
+      for (int t = cp.seg * a.K; t < cp.c0; ++t, xr += a.N * a.P) {
+        uint32_t raw[W];
+        float xv[E];
+        bload_raw<IO, E, kCM<V>>(make_rsrc(xr), lo.x, a.xes, raw);
+        raw_to_float<IO, E>(raw, xv);
+        const float z = dendrite_step<BL, L, V, FAST>(v, xv, br, alpha);
+        soma_step(h, s, z, a.beta, a.vth);
+      }
+    }
     float xin[KS][E], gsv[KS], gvv[KS];
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
@@ -1675,21 +1719,21 @@ __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo
       gvv[k] = FAST ? 0.0f : in.in.gv[k];
     }
     auto request = [&] {
-      load_visit<IO, BL, L, V, KS, !FAST, ST, FULL>(ba, lo, ld, more, nxt);
-      todo -= next_visit<KS, FULL>(a, wk, nseg, ld) ? 1 : 0;
+      load_visit<IO, BL, L, V, KS, !FAST, ST, SEG, EXACT>(ba, lo, ld, more, nxt);
+      todo -= next_visit<KS, SEG>(a, wk, nseg, ld) ? 1 : 0;
     };
     if (kEarly) request();
     __builtin_amdgcn_sched_barrier(0);
-    if (FULL || cp.i == cp.j) {
-      if ((FULL || cp.last) && cp.seg == nseg - 1) {  // the neuron's last chunk: nothing after it
+    if (SEG || cp.i == cp.j) {
+      if ((SEG || cp.last) && cp.seg == nseg - 1) {  // the neuron's last chunk: nothing after it
         bl.dh_next = 0.0f;
 #pragma unroll
         for (int j = 0; j < E; ++j) bl.lam[j] = 0.0f;
       }
       IO* const gx = static_cast<IO*>(ba.gx) + cp.nx0 + int64_t(cp.c0) * (a.N * a.P);
       Stash<BL, KS, V, (KS <= 4 || sizeof(IO) == 4)> st;
-      recompute_chunk<BL, L, V, KS, FAST, !FULL>(a, br, alpha, v, h, s, xin, st, cp.cs);
-      reverse_chunk<IO, BL, L, V, KS, !FULL, ST>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cp.cs);
+      recompute_chunk<BL, L, V, KS, FAST, kSkip>(a, br, alpha, v, h, s, xin, st, cp.cs);
+      reverse_chunk<IO, BL, L, V, KS, !EXACT, ST>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cp.cs);
     } else {
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
@@ -1705,7 +1749,7 @@ __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo
         b[SE * kThreads] = h;
       }
     }
-    next_visit<KS, FULL>(a, wk, nseg, cp);
+    next_visit<KS, SEG>(a, wk, nseg, cp);
     if (!kEarly) __builtin_amdgcn_sched_barrier(0);
     if (!kEarly && more) request();
   };
@@ -1787,12 +1831,12 @@ __device__ __forceinline__ void dma_visit_items(const BwdArgs& ba, const LaneOff
   const Walk wk = make_walk<L, kCM<V>>(a, int64_t(a.ways) * a.M);
   int todo = wk.nw * nk;  // neurons whose last visit is still to be requested
   if (todo <= 0) return;
-  VisitAt ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0, 0, 0, 0, 0, true, true};
-  enter_segment<KS>(a, ld);
+  VisitAt ld{bt0 * a.M, bt0 * a.M * a.P, nseg - 1, 0, 0, 0, 0, 0, true, true, false};
+  enter_segment<KS, !MULTI, false>(a, ld);
   VisitAt cp = ld;
   SegSmall<KS> cur;
   issue_wide_visit<IO, BL, V, KS, FAST>(ba, lo, ld, area, cur);
-  todo -= next_visit<KS, false>(a, wk, nseg, ld) ? 1 : 0;
+  todo -= next_visit<KS, !MULTI, false>(a, wk, nseg, ld) ? 1 : 0;
   BwdLane<IO, E> bl;
   bl.stage = stage;
   bl.dh_next = 0.0f;
@@ -1839,7 +1883,7 @@ __device__ __forceinline__ void dma_visit_items(const BwdArgs& ba, const LaneOff
     more = todo > 0;
     if (more) {
       issue_wide_visit<IO, BL, V, KS, FAST>(ba, lo, ld, area, cur);
-      todo -= next_visit<KS, false>(a, wk, nseg, ld) ? 1 : 0;
+      todo -= next_visit<KS, !MULTI, false>(a, wk, nseg, ld) ? 1 : 0;
     }
     if (rev) {
       Stash<BL, KS, V> st;
@@ -1854,7 +1898,7 @@ __device__ __forceinline__ void dma_visit_items(const BwdArgs& ba, const LaneOff
         soma_step(h, s, z, a.beta, a.vth);
       }
     }
-    next_visit<KS, false>(a, wk, nseg, cp);
+    next_visit<KS, !MULTI, false>(a, wk, nseg, cp);
   }
 }
 
@@ -1973,9 +2017,9 @@ __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& po
 }
 
 // Which pipeline a backward kernel runs: every neuron one chunk of exactly KS
-// steps, one chunk of at most KS, visits over segments and chunks, or over
-// segments that are one chunk of KS steps each.
-enum BwdPath { kOneChunk = 0, kPartChunk = 1, kVisits = 2, kFullSegments = 3 };
+// steps, one chunk of at most KS, visits over the chunks of segments, or over
+// segments that are one chunk each, of at most or of exactly KS steps.
+enum BwdPath { kOneChunk = 0, kPartChunk = 1, kVisits = 2, kSegments = 3, kExactSegments = 4 };
 
 // The stateful dendrite's wide fp32 lanes move their rows by LDS DMA
 // (dma_visit_items).
@@ -1988,15 +2032,16 @@ template <typename IO, int BL, int L, int V, int KS, int PATH, bool FAST, bool S
 __device__ __forceinline__ void bwd_run(const BwdArgs& ba, const LaneOff& lo, const Branches<BL, kKC<V>>& br,
                                         float alpha, int64_t bt0, int nk, Accum<BL, BL * kKC<V>>& acc,
                                         uint32_t* stage, float* bnd) {
-  if constexpr (PATH == kVisits || PATH == kFullSegments)
-    visit_items<IO, BL, L, V, KS, FAST, ST, (PATH == kFullSegments && !kWideSF<IO, BL * kKC<V>, V>)>(ba, lo, br, alpha, bt0, nk, acc, stage, bnd);
+  if constexpr (PATH >= kVisits)
+    visit_items<IO, BL, L, V, KS, FAST, ST, (PATH != kVisits), PATH == kExactSegments>(ba, lo, br, alpha, bt0, nk, acc,
+                                                                                     stage, bnd);
   else
     single_chunk_items<IO, BL, L, V, KS, FAST, ST, PATH == kPartChunk>(ba, lo, br, alpha, bt0, nk, acc, stage);
 }
 
 // One pipeline a kernel, so that each has the registers it needs: with all of
 // them in one kernel, the longest-lived one set the occupancy of every other.
-// FAST (no mask and no grad_v_soma): no per-step gate select and no grad_v_soma
+// FAST (no mask and no grad_v_soma): no per-step gate select and no branch for grad_v_soma
 // requests (bf16 ImageNet-stem layer: 434 -> 396 VALU instructions per neuron;
 // bf16 backward 1-2 % faster without the empty loads).
 template <int E, int KS, int PATH, bool FAST>
@@ -2065,32 +2110,44 @@ template <typename IO, int BL, int L, int V, int KS>
 hipError_t launch_bwd(const Plan& pl, const BwdArgs& ba, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned>(pl.ntiles * pl.G));
   const bool fast = !ba.s.mask && !ba.gv;
-  const bool one = KS == 4 ? ba.s.T == KS : ba.s.T <= KS;
 #define DENDSN_BWD(PATH, FAST) \
   { \
     dendsn_bwd_kernel<IO, BL, L, V, KS, PATH, FAST><<<grid, dim3(kThreads), pl.lds, stream>>>(ba); \
     return hipGetLastError(); \
   }
-  if constexpr (kWideSF<IO, BL * kKC<V>, V>) {  // every segment one chunk, whole or not, or else
-    if (ba.s.K <= KS) {
-      if (fast) DENDSN_BWD(kFullSegments, true)
-      DENDSN_BWD(kFullSegments, false)
+  constexpr int E = BL * kKC<V>;
+  if constexpr (!kWideSF<IO, E, V>) {
+    if (ba.s.T <= KS) {
+      if constexpr (KS == 4) {
+        if (ba.s.T == KS && fast) DENDSN_BWD(kOneChunk, true)
+        if (ba.s.T == KS) DENDSN_BWD(kOneChunk, false)
+        // One to three steps: one copy for all (a tenth of the time is at stake; as
+        // segments of a checkpointed sequence they took up to 25 % longer).
+        DENDSN_BWD(kPartChunk, false)
+      } else {
+        if (fast) DENDSN_BWD(kPartChunk, true)
+        DENDSN_BWD(kPartChunk, false)
+      }
     }
-  } else {
-    // (kFullSegments saves some of the visits' bookkeeping; it is compiled for the
-    // stateful dendrite in the compartments-innermost layout, ungated)
-    if constexpr (KS == 4) {
-      if (one && fast) DENDSN_BWD(kOneChunk, true)
-      if (one) DENDSN_BWD(kOneChunk, false)
-    } else {
-      if (one && fast) DENDSN_BWD(kPartChunk, true)
-      if (one) DENDSN_BWD(kPartChunk, false)
-    }
-    if constexpr (!kSL<V> && !kCM<V>)
-      if (fast && ba.s.K == KS && ba.s.T % KS == 0) DENDSN_BWD(kFullSegments, true)
+    // Whole segments of narrow stateful bf16 lanes, without the padding's branches
+    // (16 steps, K = 4, four branches: 234 against 249 us; K = 8, two branches of
+    // two: 222 against 261).  Wider and fp32 lanes spill there (ten bf16
+    // compartments 926 against 340 us; 64 steps fp32, K = 8: 234 against 227).
+    if constexpr (sizeof(IO) == 2 && !kSL<V> && !kCM<V> && E <= 4)
+      if (fast && ba.s.K == KS && ba.s.T % KS == 0) DENDSN_BWD(kExactSegments, true)
   }
-  if (fast) DENDSN_BWD(kVisits, true)
-  DENDSN_BWD(kVisits, false)
+  // (channel-major eight-step segments are faster as visits: 16 steps, K = 8, fp32
+  // 214 against 242 us)
+  if constexpr (!(kCM<V> && KS == 8))
+    if (ba.s.K <= KS) {
+      if (fast) DENDSN_BWD(kSegments, true)
+      DENDSN_BWD(kSegments, false)
+    }
+  if constexpr (KS == 8 || !long_stash(BL, L, kKC<V>, kCM<V>)) {
+    if (fast) DENDSN_BWD(kVisits, true)
+    DENDSN_BWD(kVisits, false)
+  }
+  return hipErrorInvalidValue;  // (the plan gives segments above 4 steps a stash of 8 where it is compiled)
 #undef DENDSN_BWD
 }
 

@@ -8,7 +8,11 @@ namespace dendsn {
 
 constexpr int kThreads = 256;  // 4 wave64s per block
 
-constexpr bool long_stash(int BL, int L, int KC, bool cm) { return BL * KC == 4 && (L <= 4 || (KC == 1 && !cm)); }
+// Mappings compiled with a backward stash of 8 steps beside that of 4.  Lanes of
+// one to three compartments too: five steps in chunks of 1 + 4 took 93 us against
+// 54 (fp32, one compartment, 784 positions, 128 channels, 32 samples), eight steps
+// of three compartments 316 against 246.
+constexpr bool long_stash(int BL, int L, int KC, bool cm) { return BL * KC <= 4 && (L <= 4 || (KC == 1 && !cm)); }
 
 // The backward translation units are compiled once per surrogate derivative
 // (-DDENDSN_SG=0: atan, 1: sigmoid), which is bit 5 of the kernel variant V; their
@@ -130,15 +134,15 @@ constexpr int variant_bits(int v) { return (v & 3) | ((v & 4) << 4); }
 // the forward and the backward may split a neuron differently and still agree
 // bit for bit.
 // Backward stash capacities: 4 steps for every mapping, and 8 steps too
-// (long_stash) where a lane holds exactly 4 compartments, over at most 4 lanes in
-// the channel-major layout and with several compartments per branch (wider or
-// narrower lanes run long sequences in chunks of 4 steps).
+// (long_stash) where a lane holds at most 4 compartments, over at most 4 lanes in
+// the channel-major layout and with several compartments per branch (wider
+// lanes run long sequences in chunks of 4 steps).
 #define DENDSN_FAST_F32(X) X(4, 1) X(4, 2) X(4, 4) X(4, 8) X(4, 16)
 // The fp32 forward also holds 8 branches per lane over two lanes (16 branches).
 #define DENDSN_FAST_F32_FWD(X) DENDSN_FAST_F32(X) X(8, 2)
 #define DENDSN_FAST_BF16(X) X(4, 1) X(8, 1) X(8, 2) X(8, 4) X(8, 8) X(8, 16)
-// The bf16 backward also holds 4 branches per lane (8 bytes) up to 64 branches.
-#define DENDSN_FAST_BF16_BWD(X) DENDSN_FAST_BF16(X) X(4, 2) X(4, 4) X(4, 8) X(4, 16)
+// The bf16 backward holds 4 branches per lane (8 bytes) from 16 up to 64 branches.
+#define DENDSN_FAST_BF16_BWD(X) X(4, 1) X(8, 1) X(8, 16) X(4, 2) X(4, 4) X(4, 8) X(4, 16)
 #define DENDSN_GENERIC(X) X(1, 1) X(2, 1) X(3, 1) X(5, 1) X(6, 1) X(7, 1) X(5, 2) X(6, 2) X(7, 2)
 
 // Compiled (BL, L, KC) mappings with KC = 2 or 4 compartments per branch (stash

@@ -471,6 +471,56 @@ def test_long_segments_match_checkpointed_ones(gpu_device, shape, variant):
     compare(case, outs[2])
 
 
+# Sequences around the backward's chunks (4 or 8 steps): shorter than one, two chunks
+# whose first is one or two steps (read by the second's visit) or longer, checkpointed
+# segments that fill a chunk exactly or not, on every kind of lane.
+# T, batch, C, S, B, k, io, layout, checkpoint intervals (0: none)
+CHUNK_EDGES = [
+    (1, 3, 5, 64, 4, 1, "bf16", "npb", (0,)),
+    (2, 3, 70, 1, 16, 1, "f32", "npb", (0, 1)),
+    (3, 2, 3, 50, 5, 2, "bf16", "npb", (0, 2)),
+    (3, 2, 4, 49, 2, 2, "f32", "channel_major", (0, 1)),
+    (5, 3, 5, 49, 1, 1, "bf16", "npb", (0, 5, 3)),             # one compartment: one chunk of 8
+    (7, 2, 3, 100, 2, 1, "f32", "channel_major", (0, 4)),
+    (8, 2, 5, 36, 3, 1, "f32", "npb", (0, 8, 5)),
+    (9, 2, 3, 100, 2, 2, "f32", "npb", (0, 8, 4)),             # 1 + 8 steps
+    (10, 3, 5, 49, 2, 2, "bf16", "channel_major", (0, 8, 5)),  # 2 + 8
+    (11, 2, 3, 64, 4, 1, "bf16", "npb", (0, 8)),               # 3 + 8: with an advance visit
+    (5, 2, 4, 64, 5, 2, "bf16", "npb", (0, 4)),                # 1 + 4, wide rows
+    (6, 2, 4, 64, 6, 1, "f32", "npb", (0, 4, 2)),              # 2 + 4
+    (6, 5, 70, 1, 5, 2, "f32", "npb", (0, 5)),                 # wide fp32, fully connected
+    (16, 2, 4, 64, 2, 2, "bf16", "npb", (0, 8, 4, 6)),         # segments of exactly one chunk, or less
+    (12, 2, 3, 64, 8, 1, "bf16", "npb", (0, 4)),
+    (12, 2, 3, 40, 7, 2, "bf16", "npb", (0, 4, 5)),
+    (18, 2, 4, 64, 4, 1, "f32", "npb", (0, 8, 9, 10)),         # the last segment shorter than the others
+]
+
+
+@pytest.mark.parametrize("shape", CHUNK_EDGES, ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}".format(*s))
+@pytest.mark.parametrize("variant", ["stateful", "stateful-mask", "stateful-gv-id", "stateless-res"])
+def test_sequences_around_the_backward_chunks(gpu_device, shape, variant):
+    """Spikes and grad_x bit for bit across checkpoint intervals, and the oracle's values."""
+    import torch
+
+    T, batch, C, S, B, k, io, layout, intervals = shape
+    base = cfg(T=T, batch=batch, C=C, S=S, B=B, comps_per_branch=k, io=io, layout=layout, beta=0.6,
+               stateful="stateless" not in variant, residual="res" in variant,
+               psi="identity" if "id" in variant else "mexhat", sg="sigmoid")
+    case = make_case(base, seed=zlib.crc32(repr((shape, variant)).encode()) % 10000, alpha=0.6,
+                     mask_rho=0.6 if "mask" in variant else None, with_gv="gv" in variant,
+                     name=f"chunk-edges/{shape}/{variant}")
+    d = to_device(case, gpu_device)
+    outs = []
+    for K in intervals:
+        case.cfg = base.with_(ckpt_every=K)
+        outs.append(run_gpu(case, gpu_device, dev=d))
+    for o in outs[1:]:
+        assert torch.equal(_bits(o["raw"]["spikes"]), _bits(outs[0]["raw"]["spikes"]))
+        assert torch.equal(_bits(o["raw"]["grads"]["grad_x"]), _bits(outs[0]["raw"]["grads"]["grad_x"]))
+    for o in outs:
+        compare(case, o)
+
+
 @pytest.mark.parametrize("shape", ["generic-kc2-S40", "fast-kc1-fc", "bf16-kc2-S300"])
 def test_stateless_checkpoint_interval_is_bit_invariant(gpu_device, shape):
     """The Stateless Dendrite checkpoints only the somatic potential; its backward
