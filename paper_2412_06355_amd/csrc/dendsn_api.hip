@@ -131,6 +131,9 @@ dendsn_status fail(dendsn_status st, const std::string& msg) {
   return st;
 }
 
+// LDS that a block's folded float64 sums may take.
+constexpr int64_t kFoldBytes = 53248;
+
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -273,6 +276,8 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   const int L = p.L;
   const int esz = c->io == DENDSN_IO_BF16 ? 2 : 4;
   p.nw = 1;
+  const int E = p.BL * p.KC;
+  const bool wide_sf = !p.cm && c->stateful && esz == 4 && E * esz > 16;  // (see the occupancy cap)
   // A tile that holds one channel's whole map (pb / 2 < S < pb) is a spatial tile in
   // the backward: its block reduction is parallel over the positions, where a kSeg
   // tile's thread adds its channel's S positions one by one (14x14 maps, 256
@@ -342,7 +347,11 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // (with the XCD eighths below: 1.5-4 % faster than two or four) and eight
   // neurons (batch items x positions) per lane for bf16 (4-5 % faster than four).
   const bool lane16 = esz == 4 && L == 1 && p.BL * p.KC * esz == 16;
-  const int64_t target_waves = (p.cm || lane16) ? 32768 : (esz == 4 ? 24576 : 16384);
+  // (eight bf16 branches over two lanes, longer sequences: a neuron's two lanes make
+  // twice the tiles, so twice the waves keep the items of a group, and with them a
+  // lane's fp32 chain, what they are for one lane)
+  const bool split8 = bwd && esz == 2 && p.KC == 1 && !p.cm && c->B == 8 && L == 2;
+  const int64_t target_waves = (p.cm || lane16 || split8) ? 32768 : (esz == 4 ? 24576 : 16384);
   int64_t G = ceil_div(target_waves, p.ntiles * 4);
   if (!bwd && p.mode == kSpatial) G = esz == 2 ? ceil_div(c->batch * p.nw, 8) : c->batch;
   // fully connected tiles (both directions): four batch items per wave (dbg: the
@@ -367,24 +376,31 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // (14x14, 256 channels, 8 samples: 8.7 -> 7.3 us; 12x12, T = 8, bf16: 16.1 -> 13.4;
   // four items 13.1 and 7.2, but 30 % slower on 4x4 maps).
   if (!bwd && p.mode == kSeg) G = std::min(G, std::max(ceil_div(1024, p.ntiles), ceil_div(c->batch, 2)));
-  // The backward over spatial tiles of one position per lane: four items a block
-  // once that leaves 512 blocks (28x28, T = 6, bf16: 50.6 -> 40.8 us; 14x14, 32
-  // samples: 93 -> 60; 16x16, 64 samples: 27.4 -> 20.5; 32x32, ten compartments:
-  // 65.3 -> 59.3).  With several positions per lane fewer groups gained and lost
-  // (32x32, 64 channels, 16 samples: 34.3 us with 16 groups, 36.4 with 4): unchanged.
-  // Fewer items where four would be more than 24 steps of one lane's fp32 sums (ten
-  // steps, ten compartments, 32x32: no faster with four than with two, and the error
-  // of g_beta twice as large).
-  if (bwd && p.mode == kSpatial && p.nw == 1) {
-    const int64_t items = std::min<int64_t>(4, std::max<int64_t>(1, 24 / c->T));
-    G = std::min(G, std::max(ceil_div(512, p.ntiles), ceil_div(c->batch, items)));
-  }
   G = std::min(G, max_g);
+  // The backward over spatial tiles of one position per lane: more items a block, up to
+  // four and up to 24 steps of work, as long as 512 blocks are left; a block's fixed
+  // cost (parameters, reduction, the first rows' wait) is that of some steps.  16x16,
+  // 128 channels, 64 samples, B = 4, T = 4: 104 -> 63 us, bf16 50 -> 38; 32x32, ten
+  // compartments, T = 10: 120 -> 109.  Over 102 drawn layers (16 to 256 channels, 4 to
+  // 128 samples, 4x4 to 64x64, 3 to 16 steps) the time against the groups above, by the
+  // limit: 12 steps 0.947, 16 0.939, 20 0.941, 24 0.943, 32 0.952, none 0.956 (16 to 24
+  // differ by less than one layer's runs); at most six items 0.973.  The items' sums are folded in float64 (fold_item), so neither a
+  // lane's fp32 chain nor the number of fp32 roundings between a lane and the output
+  // grows with the group.  With several positions per lane fewer groups gained and lost
+  // (32x32, 64 channels, 16 samples: 34.3 us with 16 groups, 36.4 with 4): unchanged.
+  // The float64 sums have to fit beside what else a block keeps in LDS.
+  const int64_t fold_bytes = int64_t(2 * p.BL + E + 2) * kThreads * 8;
+  if (bwd && p.mode == kSpatial && p.nw == 1 && !wide_sf && c->batch_groups == 0 && fold_bytes <= kFoldBytes) {
+    const int64_t items = std::min(std::min<int64_t>(4, 24 / c->T), c->batch * p.ntiles / 512);
+    if (items > ceil_div(c->batch, G)) {
+      G = ceil_div(c->batch, items);
+      p.fold = 1;
+    }
+  }
   if (c->batch_groups > 0) G = c->batch_groups < c->batch ? c->batch_groups : c->batch;
   p.bpg = int32_t(ceil_div(c->batch, G));
   p.G = int32_t(ceil_div(c->batch, p.bpg));
   p.nck = int32_t(ceil_div(c->T, c->ckpt_every) - 1);
-  const int E = p.BL * p.KC;
   p.KS = (Ke > 4 && long_stash(p.BL, p.L, p.KC, p.cm)) ? 8 : 4;
   // Occupancy cap (measured on MI355X): the backward over conv-shaped tiles whose
   // lanes move 16 bytes per row runs 3-4 % faster with at most two blocks per CU
@@ -396,23 +412,26 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // The stateful dendrite's wide fp32 lanes (more than 16 bytes of a row in a
   // lane) already hold about 70 KB of static LDS per block in the backward (the
   // DMA areas of their segment pipeline), which keeps them at two blocks per CU.
-  const bool wide_sf = !p.cm && c->stateful && esz == 4 && p.BL * p.KC * esz > 16;
   const bool cap = bwd && p.mode == kSpatial && p.BL * p.KC * esz >= 16 && (p.nw == 1 || p.L >= 2) && !wide_sf &&
                    (p.KS == 4 || p.L >= 2);
   p.lds = cap ? int32_t(163840 / 3 + 256) : 0;
   if (bwd) {
     // Chunk-start slots of segments longer than KS: (E + 1) floats a lane and
     // slot (the Stateless Dendrite: H alone), for the chunks between the first
-    // and the last.  At most 40 KB a block, then every second, fourth, ... start
+    // and the last.  At most 40 KB a block (60 KB with the folded sums), then every second, fourth, ... start
     // is kept.  The wide stateful fp32 lanes have no room beside their DMA area:
     // up to kDmaChunks chunks keep none (short segments: advancing again from
     // the segment's start costs little), more keep up to four in the area.
     const int64_t slot = int64_t((c->stateful ? E : 0) + 1) * kThreads * 4;
     const int64_t nch = ceil_div(Ke, p.KS);
-    const int64_t most = wide_sf ? (nch <= kDmaChunks ? 0 : 4) : 40960 / slot;
+    const int64_t most = wide_sf ? (nch <= kDmaChunks ? 0 : 4) : (p.fold ? 61440 - fold_bytes : 40960) / slot;
     const int64_t n = nch > 2 ? nch - 2 : 0;
     while ((n >> p.bsh) > most) ++p.bsh;
-    if (!wide_sf && (n >> p.bsh) * slot > p.lds) p.lds = int32_t((n >> p.bsh) * slot);
+    if (!wide_sf) {
+      const int64_t slots = (n >> p.bsh) * slot;  // (whole kilobytes)
+      if (p.fold) p.fold_at = int32_t(slots / 4);
+      p.lds = int32_t(std::max<int64_t>(p.lds, slots + (p.fold ? fold_bytes : 0)));
+    }
   }
   // XCD runs (blocks are dealt to the 8 XCDs round-robin; measured on MI355X):
   // fully connected tiles in runs of 32 blocks per XCD (dbg forward / backward
@@ -440,8 +459,8 @@ size_t ckpt_bytes(const dendsn_cfg* c, const Plan& p) {
 int variant_of(const dendsn_cfg* c) { return c->psi | (c->residual << 1) | ((c->stateful ? 0 : 1) << 2); }
 
 void ws_layout(const dendsn_cfg* c, const Plan& p, size_t* offA, size_t* total) {
-  const size_t nP = size_t(p.G) * size_t(p.tpc) * size_t(c->C) * size_t(2 * c->B + c->B * c->comps_per_branch);
-  const size_t nA = size_t(p.G) * size_t(p.ntiles);
+  const size_t nP = size_t(p.fold ? 2 : 1) * size_t(p.G) * size_t(p.tpc) * size_t(c->C) * size_t(2 * c->B + c->B * c->comps_per_branch);
+  const size_t nA = size_t(p.fold ? 2 : 1) * size_t(p.G) * size_t(p.ntiles);
   *offA = ((nP * sizeof(float) + 255) / 256) * 256;
   *total = *offA + 2 * nA * sizeof(float);  // g_alpha partials, then g_beta partials
 }
@@ -685,8 +704,10 @@ dendsn_status backward_impl(const dendsn_cfg* cfg, const void* x, const float* a
   ba.gx = grad_x;
   ba.wsP = static_cast<float*>(workspace);
   ba.wsA = reinterpret_cast<float*>(static_cast<char*>(workspace) + offA);
-  ba.wsB = ba.wsA + int64_t(p.G) * p.ntiles;
-  ba.slots = int64_t(p.G) * p.tpc;
+  const int64_t per = p.fold ? 2 : 1;  // slots of a partial
+  ba.fold = p.fold; ba.fold_at = p.fold_at;
+  ba.wsB = ba.wsA + per * p.G * p.ntiles;
+  ba.slots = per * p.G * p.tpc;
   ba.wide = ba.slots > kNarrowSlots;
   ba.detach = cfg->detach_reset;
   ba.sg_scale = cfg->sg_scale;
@@ -709,7 +730,7 @@ dendsn_status backward_impl(const dendsn_cfg* cfg, const void* x, const float* a
   f.gk = grad_kappa; f.gxi = grad_xi; f.gz = grad_zeta; f.ga = grad_alpha; f.gb = grad_beta;
   f.C = cfg->C; f.B = cfg->B; f.P = ba.s.P; f.KC = p.KC; f.slots = ba.slots; f.wide = ba.wide;
   f.stateful = cfg->stateful;
-  f.nA = int64_t(p.G) * p.ntiles;
+  f.nA = per * p.G * p.ntiles;
   const int64_t nout = cfg->C * (2 * cfg->B + ba.s.P);
   const int64_t nblk = (f.wide ? ceil_div(nout, kThreads / 64) : ceil_div(nout, kThreads)) + 2;
   dendsn_finalize_kernel<<<dim3(unsigned(nblk)), dim3(kThreads), 0, stream>>>(f);

@@ -1250,6 +1250,36 @@ struct Accum {
   float b;   // g_beta terms of this lane's neuron (counted by its first lane only)
 };
 
+// Groups of several batch items (Plan::fold): after each item the lane's sums join
+// float64 sums in LDS and start again, so a lane's fp32 chain stays one item long
+// whatever the group holds.  The order of the values: g_kappa, g_xi, g_zeta of the
+// lane as in Accum, then g_alpha and g_beta.
+template <int BL, int E>
+constexpr int kFoldValues = 2 * BL + E + 2;
+
+__device__ __forceinline__ double* fold_sums(const BwdArgs& ba) {
+  extern __shared__ __align__(16) float slots[];
+  return reinterpret_cast<double*>(slots + ba.fold_at);
+}
+
+template <int BL, int E>
+__device__ __forceinline__ void fold_item(const BwdArgs& ba, Accum<BL, E>& acc) {
+  if (!ba.fold) return;
+  double* d = fold_sums(ba) + threadIdx.x;
+  auto join = [&](int i, float& v) {
+    d[i * kThreads] += double(v);
+    v = 0.0f;
+  };
+#pragma unroll
+  for (int j = 0; j < BL; ++j) join(j, acc.k[j]);
+#pragma unroll
+  for (int i = 0; i < E; ++i) join(BL + i, acc.xi[i]);
+#pragma unroll
+  for (int j = 0; j < BL; ++j) join(BL + E + j, acc.z[j]);
+  join(2 * BL + E, acc.a);
+  join(2 * BL + E + 1, acc.b);
+}
+
 template <typename IO, int E>
 struct BwdLane {  // adjoint state carried backwards through time, and pointers
   float dh_next;
@@ -1506,6 +1536,7 @@ __device__ __forceinline__ void single_chunk_items(const BwdArgs& ba, const Lane
     Stash<BL, KS, V, (KS <= 4)> st;
     recompute_chunk<BL, L, V, KS, FAST, PART>(a, br, alpha, zero, 0.0f, false, xin, st, cs);
     reverse_chunk<IO, BL, L, V, KS, PART, ST>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cs);
+    fold_item<BL, E>(ba, acc);
   };
   for (int i = 0; i + 1 < nvis; ++i) {
     ChunkRaw<IO, E, KS, kCM<V>, ST> nxt;
@@ -1734,6 +1765,7 @@ __device__ __forceinline__ void visit_items(const BwdArgs& ba, const LaneOff& lo
       Stash<BL, KS, V, (KS <= 4 || sizeof(IO) == 4)> st;
       recompute_chunk<BL, L, V, KS, FAST, kSkip>(a, br, alpha, v, h, s, xin, st, cp.cs);
       reverse_chunk<IO, BL, L, V, KS, !EXACT, ST>(ba, lo, br, alpha, beta_r, gx, st, gsv, gvv, bl, acc, cp.cs);
+      if (cp.seg == 0 && (SEG || cp.j == 0)) fold_item<BL, E>(ba, acc);  // the neuron's first step is done
     } else {
 #pragma unroll
       for (int k = 0; k < KS; ++k) {
@@ -1939,6 +1971,38 @@ __device__ __forceinline__ void output_source(int o, int B, int P, int* sub, int
   }
 }
 
+// Block reduction of the folded float64 sums (spatial tiles), in a fixed order: 16
+// lanes per output.  A partial leaves as two floats, its value and what rounding
+// that left over, in two adjacent slots, so the sum over slots loses nothing.
+template <int BL, int E, int L>
+__device__ __forceinline__ void reduce_folded(const BwdArgs& ba, const Pos& pos) {
+  const ScanArgs& a = ba.s;
+  const int B = a.B, P = a.P, W = 2 * B + P;
+  const double* d = fold_sums(ba);
+  const int r = threadIdx.x & 15;
+  __syncthreads();
+  for (int o = threadIdx.x >> 4; o < W + 2; o += kThreads / 16) {
+    int sub = 0, v = 2 * BL + E + (o - W), step = o == W ? 1 : L;  // g_alpha: every lane; g_beta: the neuron's first
+    if (o < W) output_source<BL, E>(o, B, P, &sub, &v);
+    double s = 0.0;
+    for (int q = r * step; q < kThreads; q += 16 * step) s += d[v * kThreads + q + sub];
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if (r == 0) {
+      const float hi = float(s), lo = float(s - double(hi));
+      if (o < W) {
+        const int64_t p = 2 * (int64_t(pos.g) * a.tpc + pos.tile % a.tpc);
+        ba.wsP[partial_index(ba, pos.c, o, p)] = hi;
+        ba.wsP[partial_index(ba, pos.c, o, p + 1)] = lo;
+      } else {
+        float* w = (o == W ? ba.wsA : ba.wsB) + 2 * (int64_t(pos.g) * a.ntiles + pos.tile);
+        w[0] = hi;
+        w[1] = lo;
+      }
+    }
+  }
+}
+
 // Block reduction of the parameter-gradient partials, in a fixed order.
 template <int BL, int E, int L>
 __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& pos, Accum<BL, E>& acc) {
@@ -2067,6 +2131,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(k
   for (int i = 0; i < E; ++i) acc.xi[i] = 0.0f;
   acc.a = 0.0f;
   acc.b = 0.0f;
+  if (!kDma && ba.fold) {
+#pragma unroll
+    for (int i = 0; i < kFoldValues<BL, E>; ++i) fold_sums(ba)[i * kThreads + threadIdx.x] = 0.0;
+  }
   if (pos.active) {
     Branches<BL, kKC<V>> br;
     load_branches<BL, kKC<V>>(a, pos.c, pos.sub, br);
@@ -2074,7 +2142,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(k
     LaneOff lo = lane_offsets<IO, E, kCM<V>>(a, pos);
     int64_t bt0;
     const int nk = items_of(a, pos, &bt0);
-    extern __shared__ float slots[];
+    extern __shared__ __align__(16) float slots[];
     float* bnd = slots;  // chunk-start states of segments longer than KS (see visit_items)
     bool done = false;
     if constexpr (kWide) {
@@ -2100,6 +2168,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(k
       }
     }
     if (!done) bwd_run<IO, BL, L, V, KS, PATH, FAST, false>(ba, lo, br, alpha, bt0, nk, acc, nullptr, bnd);
+  }
+  if (!kDma && ba.fold) {  // (block-uniform)
+    reduce_folded<BL, E, L>(ba, pos);
+    return;
   }
   if (pos.sub != 0) acc.b = 0.0f;  // the soma runs in every lane of a neuron: count it once
   // every thread of the block reaches this one call (it holds block barriers)

@@ -49,6 +49,8 @@ struct Plan {
   int32_t lds;    // dynamic LDS bytes per block: chunk-start slots of the backward, or room
                   // reserved only to cap blocks per CU
   int32_t bsh;    // the slots keep every (1 << bsh)-th chunk start of a segment
+  int32_t fold;   // 1: a backward group's items are summed in float64 (two partial slots a group)
+  int32_t fold_at;  // where in the dynamic LDS those sums lie (floats)
   int32_t nw;     // positions per lane and batch item in spatial tiles (1, 2 or 4)
   int32_t xk;     // XCD runs: consecutive tiles per XCD turn (1: plain round-robin)
 };
@@ -92,10 +94,11 @@ struct BwdArgs {
   const float* gv;  // optional
   void* gx;
   float* wsP;       // partial sums of (g_kappa, g_xi, g_zeta): `slots` per output, see partial_index
-  float* wsA;       // [G][ntiles] partial sums of g_alpha
-  float* wsB;       // [G][ntiles] partial sums of g_beta
-  int64_t slots;    // partial slots per output: G * tpc
+  float* wsA;       // [G][ntiles] partial sums of g_alpha ([G][ntiles][2] with fold)
+  float* wsB;       // the same of g_beta
+  int64_t slots;    // partial slots per output: G * tpc, twice that with fold
   int32_t wide;     // 1: output-major layout (slots > kNarrowSlots)
+  int32_t fold, fold_at;  // see Plan
   int32_t detach;
   float sg_scale;
   const float* gvz;  // grad_v_soma, or any address when absent

@@ -704,6 +704,66 @@ def test_small_layers_tiles_and_groups(gpu_device, shape, variant):
     assert torch.equal(_bits(a["raw"]["grads"]["grad_x"]), _bits(b["raw"]["grads"]["grad_x"]))
 
 
+# --- backward groups of several items whose sums are folded in float64: every lane
+# count and pipeline (T, batch, C, S, B, k, io, layout, K) ---
+FOLDED = [
+    (6, 64, 16, 256, 2, 2, "f32", "npb", 0),
+    (4, 128, 16, 256, 2, 2, "bf16", "channel_major", 0),
+    (33, 64, 16, 256, 4, 1, "bf16", "npb", 0),        # chunk starts and folded sums in LDS
+    (16, 64, 16, 256, 4, 1, "f32", "npb", 4),         # segments
+    (10, 64, 16, 256, 2, 2, "f32", "channel_major", 0),
+    (3, 64, 16, 300, 5, 2, "bf16", "npb", 0),         # wide rows, two tiles a channel
+    (6, 128, 8, 129, 2, 2, "f32", "npb", 0),          # one map a tile, idle lanes
+    (6, 128, 16, 128, 8, 1, "f32", "npb", 0),         # two lanes per neuron
+    (6, 128, 16, 64, 16, 1, "bf16", "npb", 0),        # four
+    (5, 512, 3, 300, 3, 1, "f32", "npb", 0),
+]
+
+
+@pytest.mark.parametrize("shape", FOLDED, ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}-K{}".format(*s))
+@pytest.mark.parametrize("variant", ["stateful", "stateless-res-mask"])
+def test_items_of_a_group_are_summed_apart(gpu_device, shape, variant):
+    """Neighbouring items with the same inputs and opposite spike gradients have exactly
+    opposite parameter gradients (every operation rounds symmetrically), so where each
+    item's float32 sums are formed apart, the layer's are exactly zero; one float32
+    chain through a group's items would leave rounding errors of about 1e-7 of an item's."""
+    import torch
+
+    T, batch, C, S, B, k, io, layout, K = shape
+    c = cfg(T=T, batch=batch, C=C, S=S, B=B, comps_per_branch=k, io=io, layout=layout, ckpt_every=K, beta=0.6,
+            stateful="stateless" not in variant, residual="res" in variant)
+    one_item = c.with_(batch_groups=batch)
+    assert dendsn.dendsn_bwd_workspace_bytes(c) <= dendsn.dendsn_bwd_workspace_bytes(one_item)
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(zlib.crc32(repr((shape, variant)).encode()))
+    dt = torch.bfloat16 if io == "bf16" else torch.float32
+    announce(f"folded/{shape}/{variant}")
+    x = torch.randn((T, batch // 2, 1, C * S * B * k), device=gpu_device, generator=g).to(dt)
+    x = x.expand(T, batch // 2, 2, C * S * B * k).contiguous()
+    x = x.view((T, batch, C, B * k, S) if layout == "channel_major" else (T, c.N, c.P))
+    gs = torch.randn((T, batch // 2, 1, C * S), device=gpu_device, generator=g).to(dt)
+    gs = torch.cat([gs, -gs], dim=2).view(T, c.N).contiguous()
+    alpha = torch.full((1,), 0.6, device=gpu_device)
+    kappa = torch.rand((C, B), device=gpu_device, generator=g)
+    xi = torch.randn((C, B * k), device=gpu_device, generator=g) * 0.5
+    mask = (torch.rand((C, B), device=gpu_device, generator=g) < 0.7).to(torch.uint8) if "mask" in variant else None
+    _, _, ckpt = dendsn.forward(c, x, alpha, kappa, xi, None, mask)
+    out = dendsn.backward(c, x, alpha, kappa, xi, None, mask, ckpt, gs)
+    for name in ("grad_alpha", "grad_beta", "grad_kappa", "grad_xi", "grad_zeta"):
+        assert not out[name].any(), (name, out[name].abs().max().item())
+    # and with unrelated gradients, the sums of one-item groups
+    gs = torch.randn((T, c.N), device=gpu_device, generator=g).to(dt)
+    a = dendsn.backward(c, x, alpha, kappa, xi, None, mask, ckpt, gs)
+    b = dendsn.backward(one_item, x, alpha, kappa, xi, None, mask, ckpt, gs)
+    assert torch.equal(_bits(a["grad_x"]), _bits(b["grad_x"]))
+    for name in ("grad_kappa", "grad_xi", "grad_zeta"):
+        # one-item groups round each item's wave and block sums (at most 10 additions
+        # deep) to 2^-24 of their size; the items' sizes add up as random signs do, and
+        # an output is much smaller than that on few elements
+        tol = 10 * 2.0 ** -24 * batch ** 0.5 * b[name].abs().max()
+        assert (a[name] - b[name]).abs().max() <= tol, name
+
+
 def test_forward_without_checkpoints_for_inference(gpu_device):
     import torch
 
