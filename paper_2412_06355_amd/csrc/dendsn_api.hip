@@ -284,10 +284,12 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // channels, 8 samples, B = 4: backward 82.5 -> 18.2 us with the groups below).
   // Smaller maps, two or more channels a tile, stay kSeg: 11x11 maps of ten
   // compartments, T = 10, 74 us against 88, B = 8 on 7x7 51 against 57-77.
-  // One lane per neuron with rows of at most 16 bytes takes one from 7/16 of a tile on
-  // (11x11, 128 channels, 64 samples, two branches of two: backward 53.7 -> 48.1 us
-  // channel-major, 45.2 -> 43.4 otherwise); with idle waves in half the block, smaller
-  // maps lose what the reduction gains.
+  // With one lane per neuron and rows of at most 16 bytes, from 7/16 of a tile on: the
+  // smallest size at which none of seven layers lost (8 to 128 samples, 32 to 512
+  // channels, both data types and layouts; whole-channel over spatial tile, worst and
+  // geometric mean): 64 positions 0.79 and 0.96, 81 0.79 and 1.04, 100 0.93 and 1.25,
+  // 110 0.95 and 1.30, 121 1.01 and 1.36, 144 1.38 and 1.93.  Below, the idle half of
+  // the block costs layers that fill the chip what the reduction gains.
   const bool one_map = 2 * c->S > kThreads / L || (L == 1 && p.BL * p.KC * esz <= 16 && 16 * c->S >= 7 * kThreads);
   if (c->S >= kThreads / L || (bwd && one_map)) {
     p.mode = kSpatial; p.ways = 1; p.pb = kThreads / L;
@@ -362,20 +364,32 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   if (G > max_g) G = max_g;
   if (bwd && p.mode != kSpatial && G > 8) G = 8;  // bounds the per-group partials
   // Small layers (GPU time per launch, MI355X).  Fully connected tiles and the
-  // backward's kSeg tiles: at least two blocks per CU, down to one batch item a
+  // backward's kSeg tiles: about two blocks per CU, down to one batch item a
   // wave (four branches, 128 channels, 512 samples: forward 4.9 -> 3.5 us, backward
   // 21.4 -> 9.6; five branches of two, 700 channels, 300 samples, T = 10:
   // 144.8 -> 82.4; 4x4 maps, 256 channels, 128 samples, bf16: 57.7 -> 29.7).  Past
-  // that the per-block reduction and the partials cost more than they hide (500
-  // channels: 64 groups 10.9, 128 groups 15.6), and a layer that fills the chip
-  // already keeps its groups.  The partials stay below 15 MiB (fewer than 1024
-  // blocks of at most 256 / (L S) channels).
+  // that the per-block reduction and the partials cost more than they hide, and a
+  // layer that fills the chip already keeps its groups.  Over kSeg tiles no more than
+  // 512 blocks: a few beyond what is resident are a round of their own (7x7, B = 8
+  // bf16, 531 blocks 78 us, 472 65).  In the backward with many outputs no more than
+  // kNarrowSlots partials each: the output-major layout above that writes and reads
+  // them in single words (140 samples, 1602 channels, B = 8 bf16: 20 groups 30 us, 9
+  // groups 19; with few outputs more groups win: 69 channels, 134 samples 14.7 -> 9.0).
   const bool fill = p.mode == kFC || (bwd && p.mode == kSeg);
-  if (fill) G = std::max(G, ceil_div(512, p.ntiles));
-  // The forward over kSeg tiles: two items a wave once that leaves 1024 blocks
-  // (14x14, 256 channels, 8 samples: 8.7 -> 7.3 us; 12x12, T = 8, bf16: 16.1 -> 13.4;
-  // four items 13.1 and 7.2, but 30 % slower on 4x4 maps).
-  if (!bwd && p.mode == kSeg) G = std::min(G, std::max(ceil_div(1024, p.ntiles), ceil_div(c->batch, 2)));
+  if (fill) {
+    int64_t want = p.mode == kFC ? ceil_div(512, p.ntiles) : 512 / p.ntiles;
+    if (bwd && c->C * (2 * c->B + c->B * p.KC) > 16384) want = std::min<int64_t>(want, kNarrowSlots);
+    G = std::max(G, want);
+  }
+  // The forward over kSeg tiles: two items a wave where that leaves 1024 blocks, up to
+  // eight steps (14x14, 256 channels, 8 samples: 8.7 -> 7.3 us; 12x12, T = 8, bf16: 16.1
+  // -> 13.4; four items 13.1 and 7.2, but 30 % slower on 4x4 maps; with fewer blocks, 64
+  // samples of 24 to 36 positions, 6.3 -> 6.8; ten steps and more 3-8 % slower).
+  if (!bwd && p.mode == kSeg && c->T <= 8 && c->batch * p.ntiles >= 2048) G = std::min(G, ceil_div(c->batch, 2));
+  // One map a tile on the stateful dendrite's wide fp32 lanes (LDS DMA): groups as
+  // for whole-channel tiles (12x12, 64 channels, 128 samples, three branches of two:
+  // 76 -> 62 us against 64 groups, whole-channel tiles 70).
+  if (bwd && p.mode == kSpatial && c->S < p.pb && wide_sf) G = std::min(G, std::max<int64_t>(8, ceil_div(512, p.ntiles)));
   G = std::min(G, max_g);
   // The backward over spatial tiles of one position per lane: more items a block, up to
   // four and up to 24 steps of work, as long as 512 blocks are left; a block's fixed
