@@ -2108,11 +2108,16 @@ __device__ __forceinline__ void bwd_run(const BwdArgs& ba, const LaneOff& lo, co
 // FAST (no mask and no grad_v_soma): no per-step gate select and no branch for grad_v_soma
 // requests (bf16 ImageNet-stem layer: 434 -> 396 VALU instructions per neuron;
 // bf16 backward 1-2 % faster without the empty loads).
-template <int E, int KS, int PATH, bool FAST>
-constexpr int kBwdWaves = E * KS <= 8 ? 4 : (E * KS <= 16 || (FAST && PATH == kPartChunk && E <= 4) ? 3 : 2);
+// One chunk of up to eight steps gets a third wave per SIMD, seven to nine registers
+// spilled where a lane holds four compartments: channel-major bf16 rows 157 -> 138 us
+// (six steps), but compartments-innermost fp32 rows, sixteen branches, eight steps 70
+// -> 74, so those keep two.
+template <typename IO, int E, bool CM, int KS, int PATH, bool FAST>
+constexpr int kBwdWaves = E * KS <= 8 ? 4
+                          : E * KS <= 16 || (FAST && PATH == kPartChunk && (E <= 3 || (E == 4 && (sizeof(IO) == 2 || CM)))) ? 3 : 2;
 
 template <typename IO, int BL, int L, int V, int KS, int PATH, bool FAST>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kBwdWaves<BL * kKC<V>, KS, PATH, FAST>))) dendsn_bwd_kernel(BwdArgs ba) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kBwdWaves<IO, BL * kKC<V>, kCM<V>, KS, PATH, FAST>))) dendsn_bwd_kernel(BwdArgs ba) {
   constexpr int E = BL * kKC<V>;
   constexpr int W = kRawW<IO, E, kCM<V>>;
   // Staged wide rows (see load_pieces) for the Stateless Dendrite's pipelines:
