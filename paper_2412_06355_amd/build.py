@@ -19,12 +19,14 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdendsn.so")
 
 # (source, extra flags, object name).  The backward units compile once per
-# surrogate derivative (-DDENDSN_SG=0: atan, 1: sigmoid); the heaviest first.
-_BWD = ["dendsn_bwd_bf16.hip", "dendsn_bwd_bf16_kc.hip", "dendsn_bwd_f32.hip", "dendsn_bwd_f32_kc.hip",
-        "dendsn_bwd_f32_cm.hip", "dendsn_bwd_bf16_cm.hip"]
+# surrogate derivative (-DDENDSN_SG=0: atan, 1: sigmoid) and dendrite (-DDENDSN_SL=0:
+# stateful, 1: Stateless); the heaviest first.
+_BWD = ["dendsn_bwd_f32_cm.hip", "dendsn_bwd_bf16_cm.hip", "dendsn_bwd_bf16_kc.hip", "dendsn_bwd_f32_kc.hip",
+        "dendsn_bwd_bf16.hip", "dendsn_bwd_f32.hip"]
 _OTHER = ["dendsn_fwd_f32_cm.hip", "dendsn_fwd_bf16_cm.hip", "dendsn_fwd_f32_kc.hip", "dendsn_fwd_bf16_kc.hip",
           "dendsn_api.hip", "dendsn_fwd_f32.hip", "dendsn_fwd_bf16.hip"]
-SOURCES = [(src, [f"-DDENDSN_SG={k}"], f"{src[:-4]}_sg{k}.o") for src in _BWD for k in (0, 1)] + \
+SOURCES = [(src, [f"-DDENDSN_SG={k}", f"-DDENDSN_SL={m}"], f"{src[:-4]}_sg{k}_sl{m}.o")
+           for src in _BWD for m in (0, 1) for k in (0, 1)] + \
           [(src, [], f"{src[:-4]}.o") for src in _OTHER]
 
 ARCH = "gfx950"
@@ -32,9 +34,11 @@ HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=off: the forward kernel and the backward's recompute must round
 # every operation the same way; fused multiply-adds are written out as fmaf.
-# Packed FP32 instructions are disabled.
+# Packed FP32 instructions are disabled.  --offload-compress: the code objects are
+# stored compressed and unpacked when a unit's first kernel is loaded.
 CFLAGS = [
     f"--offload-arch={ARCH}",
+    "--offload-compress",
     "-O3",
     "-std=c++17",
     "-fPIC",

@@ -14,22 +14,26 @@ namespace dendsn {
 
 hipError_t launch_fwd_f32(const Plan& pl, const FwdArgs& fa, int psi, hipStream_t stream);
 hipError_t launch_fwd_bf16(const Plan& pl, const FwdArgs& fa, int psi, hipStream_t stream);
-hipError_t launch_bwd_f32_sg0(const Plan& pl, const BwdArgs& ba, int psi, hipStream_t stream);
-hipError_t launch_bwd_f32_sg1(const Plan& pl, const BwdArgs& ba, int psi, hipStream_t stream);
-hipError_t launch_bwd_bf16_sg0(const Plan& pl, const BwdArgs& ba, int psi, hipStream_t stream);
-hipError_t launch_bwd_bf16_sg1(const Plan& pl, const BwdArgs& ba, int psi, hipStream_t stream);
 hipError_t launch_fwd_f32_kc(const Plan& pl, const FwdArgs& fa, int v, hipStream_t stream);
 hipError_t launch_fwd_bf16_kc(const Plan& pl, const FwdArgs& fa, int v, hipStream_t stream);
-hipError_t launch_bwd_f32_kc_sg0(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
-hipError_t launch_bwd_f32_kc_sg1(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
-hipError_t launch_bwd_bf16_kc_sg0(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
-hipError_t launch_bwd_bf16_kc_sg1(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
 hipError_t launch_fwd_f32_cm(const Plan& pl, const FwdArgs& fa, int v, hipStream_t stream);
 hipError_t launch_fwd_bf16_cm(const Plan& pl, const FwdArgs& fa, int v, hipStream_t stream);
-hipError_t launch_bwd_f32_cm_sg0(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
-hipError_t launch_bwd_f32_cm_sg1(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
-hipError_t launch_bwd_bf16_cm_sg0(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
-hipError_t launch_bwd_bf16_cm_sg1(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);
+
+// The backward's launchers, one per unit (see DENDSN_SG_NAME).
+#define DENDSN_BWD_UNITS(k, m)                                                                          \
+  hipError_t launch_bwd_f32_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);     \
+  hipError_t launch_bwd_bf16_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);    \
+  hipError_t launch_bwd_f32_kc_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);  \
+  hipError_t launch_bwd_bf16_kc_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream); \
+  hipError_t launch_bwd_f32_cm_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream);  \
+  hipError_t launch_bwd_bf16_cm_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, hipStream_t stream); \
+  static hipError_t launch_bwd_sg##k##_sl##m(const Plan& pl, const BwdArgs& ba, int v, bool bf, hipStream_t stream) { \
+    if (pl.cm) return bf ? launch_bwd_bf16_cm_sg##k##_sl##m(pl, ba, v, stream) : launch_bwd_f32_cm_sg##k##_sl##m(pl, ba, v, stream); \
+    if (pl.KC == 1) return bf ? launch_bwd_bf16_sg##k##_sl##m(pl, ba, v, stream) : launch_bwd_f32_sg##k##_sl##m(pl, ba, v, stream); \
+    return bf ? launch_bwd_bf16_kc_sg##k##_sl##m(pl, ba, v, stream) : launch_bwd_f32_kc_sg##k##_sl##m(pl, ba, v, stream); \
+  }
+DENDSN_BWD_UNITS(0, 0) DENDSN_BWD_UNITS(0, 1) DENDSN_BWD_UNITS(1, 0) DENDSN_BWD_UNITS(1, 1)
+#undef DENDSN_BWD_UNITS
 
 // Fixed-order float64 sums of the per-block partials into the parameter
 // gradients.  Outputs o = c * W + ol with W = 2 B + P: ol < B is g_kappa of
@@ -727,15 +731,9 @@ dendsn_status backward_impl(const dendsn_cfg* cfg, const void* x, const float* a
   ba.sg_scale = cfg->sg_scale;
   const int v = variant_of(cfg);
   const bool bf = cfg->io == DENDSN_IO_BF16;
-  hipError_t e;
-  if (cfg->sg == DENDSN_SG_SIGMOID)
-    e = p.cm ? (bf ? launch_bwd_bf16_cm_sg1(p, ba, v, stream) : launch_bwd_f32_cm_sg1(p, ba, v, stream))
-        : p.KC == 1 ? (bf ? launch_bwd_bf16_sg1(p, ba, v, stream) : launch_bwd_f32_sg1(p, ba, v, stream))
-                    : (bf ? launch_bwd_bf16_kc_sg1(p, ba, v, stream) : launch_bwd_f32_kc_sg1(p, ba, v, stream));
-  else
-    e = p.cm ? (bf ? launch_bwd_bf16_cm_sg0(p, ba, v, stream) : launch_bwd_f32_cm_sg0(p, ba, v, stream))
-        : p.KC == 1 ? (bf ? launch_bwd_bf16_sg0(p, ba, v, stream) : launch_bwd_f32_sg0(p, ba, v, stream))
-                    : (bf ? launch_bwd_bf16_kc_sg0(p, ba, v, stream) : launch_bwd_f32_kc_sg0(p, ba, v, stream));
+  const bool sig = cfg->sg == DENDSN_SG_SIGMOID;
+  hipError_t e = cfg->stateful ? (sig ? launch_bwd_sg1_sl0(p, ba, v, bf, stream) : launch_bwd_sg0_sl0(p, ba, v, bf, stream))
+                               : (sig ? launch_bwd_sg1_sl1(p, ba, v, bf, stream) : launch_bwd_sg0_sl1(p, ba, v, bf, stream));
   if (e != hipSuccess) return fail(DENDSN_E_HIP, std::string("backward launch: ") + hipGetErrorString(e));
 
   FinArgs f;

@@ -7,8 +7,8 @@
 // stateless << 2, mapped by variant_bits).
 #include "dendsn_kernels.h"
 
-#ifndef DENDSN_SG
-#error "compile once per surrogate: -DDENDSN_SG=0 (atan) or 1 (sigmoid)"
+#if !defined(DENDSN_SG) || !defined(DENDSN_SL)
+#error "compile once per surrogate, -DDENDSN_SG=0 (atan) or 1 (sigmoid), and dendrite, -DDENDSN_SL=0 or 1 (Stateless)"
 #endif
 
 namespace dendsn {
@@ -21,7 +21,7 @@ static hipError_t launch_bwd_cm_v(const Plan& pl, const BwdArgs& ba, int v, hipS
   switch (v & 7) {
 #define DENDSN_V(n) \
     case n: return launch_bwd<float, BL, L, kVS | VK | variant_bits(n), KS>(pl, ba, stream);
-    DENDSN_EACH_VARIANT(DENDSN_V)
+    DENDSN_EACH_UNIT_VARIANT(DENDSN_V)
 #undef DENDSN_V
   }
   return hipErrorInvalidValue;

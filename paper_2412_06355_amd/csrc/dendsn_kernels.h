@@ -1945,20 +1945,8 @@ __device__ __forceinline__ int64_t partial_index(const BwdArgs& ba, int64_t c, i
   return ba.wide ? g * ba.slots + p : p * (ba.s.C * W) + g;
 }
 
-// A lane's NV = 2 BL + E accumulators, v = 0 .. NV-1: g_kappa of its BL
-// branches, g_xi of its E compartments, g_zeta of its branches.
-template <int BL, int E>
-__device__ __forceinline__ float accum_value(const Accum<BL, E>& acc, int v) {
-  float r = 0.0f;
-#pragma unroll
-  for (int j = 0; j < BL; ++j) r = v == j ? acc.k[j] : r;
-#pragma unroll
-  for (int i = 0; i < E; ++i) r = v == BL + i ? acc.xi[i] : r;
-#pragma unroll
-  for (int j = 0; j < BL; ++j) r = v == BL + E + j ? acc.z[j] : r;
-  return r;
-}
-
+// A lane has 2 BL + E accumulators, v = 0, 1, ...: g_kappa of its BL branches,
+// g_xi of its E compartments, g_zeta of its branches.
 // Channel output o (0 .. W-1) -> (lane-in-neuron sub, accumulator index v).
 template <int BL, int E>
 __device__ __forceinline__ void output_source(int o, int B, int P, int* sub, int* v) {
@@ -2006,7 +1994,6 @@ __device__ __forceinline__ void reduce_folded(const BwdArgs& ba, const Pos& pos)
 // Block reduction of the parameter-gradient partials, in a fixed order.
 template <int BL, int E, int L>
 __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& pos, Accum<BL, E>& acc) {
-  constexpr int NV = 2 * BL + E;
   const ScanArgs& a = ba.s;
   __shared__ float red[kThreads * E];
   __shared__ float reda[kThreads / 64];
@@ -2030,13 +2017,17 @@ __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& po
     // One channel per block: sum lanes of equal sub within the wave, then waves.
     const int64_t c = pos.c;
     const int64_t jt = pos.tile % a.tpc;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      float x = accum_value(acc, v);
+    auto sum = [&](int v, float x) {
 #pragma unroll
       for (int off = 32; off >= L; off >>= 1) x += __shfl_xor(x, off);
       if (lane < L) red[(v * 4 + wave) * L + lane] = x;
-    }
+    };
+#pragma unroll
+    for (int j = 0; j < BL; ++j) sum(j, acc.k[j]);
+#pragma unroll
+    for (int i = 0; i < E; ++i) sum(BL + i, acc.xi[i]);
+#pragma unroll
+    for (int j = 0; j < BL; ++j) sum(BL + E + j, acc.z[j]);
     __syncthreads();
     for (int o = tid; o < W; o += kThreads) {
       int sub, v;
@@ -2048,14 +2039,11 @@ __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& po
   } else {
     // Whole channels per tile: sum the batch ways and the S positions of each
     // channel, one accumulator kind (kappa, xi, zeta) at a time.
-    for (int q = 0; q < 3; ++q) {
-      const int nq = q == 1 ? E : BL;         // accumulators of this kind per lane
-      const int v0 = q == 0 ? 0 : (q == 1 ? BL : BL + E);
-      const int o0 = q == 0 ? 0 : (q == 1 ? B : B + P);
-      const int wq = q == 1 ? P : B;          // outputs of this kind per channel
+    // o0, wq: the kind's first output and number of outputs per channel
+    auto kind = [&](const auto& vals, int o0, int wq) {
+      constexpr int nq = sizeof(vals) / sizeof(float);  // accumulators of this kind per lane
 #pragma unroll
-      for (int j = 0; j < E; ++j)
-        if (j < nq) red[tid * E + j] = accum_value(acc, v0 + j);
+      for (int j = 0; j < nq; ++j) red[tid * E + j] = vals[j];
       __syncthreads();
       for (int o = tid; o < a.cpt * wq; o += kThreads) {
         const int slot = o / wq, ol = o % wq;
@@ -2071,7 +2059,10 @@ __device__ __forceinline__ void reduce_partials(const BwdArgs& ba, const Pos& po
         ba.wsP[partial_index(ba, c, o0 + ol, pos.g)] = sum;
       }
       __syncthreads();
-    }
+    };
+    kind(acc.k, 0, B);
+    kind(acc.xi, B, P);
+    kind(acc.z, B + P, B);
   }
   __syncthreads();
   if (tid == 0) {
@@ -2220,11 +2211,12 @@ hipError_t launch_bwd(const Plan& pl, const BwdArgs& ba, hipStream_t stream) {
       if (fast) DENDSN_BWD(kSegments, true)
       DENDSN_BWD(kSegments, false)
     }
-  if constexpr (KS == 8 || !long_stash(BL, L, kKC<V>, kCM<V>)) {
+  // (eight bf16 branches run longer segments over two lanes)
+  if constexpr (KS == 8 || !(long_stash(BL, L, kKC<V>, kCM<V>) || (BL == 8 && L == 1 && kKC<V> == 1))) {
     if (fast) DENDSN_BWD(kVisits, true)
     DENDSN_BWD(kVisits, false)
   }
-  return hipErrorInvalidValue;  // (the plan gives segments above 4 steps a stash of 8 where it is compiled)
+  return hipErrorInvalidValue;  // (the plan gives segments above 4 steps a mapping and stash compiled for them)
 #undef DENDSN_BWD
 }
 

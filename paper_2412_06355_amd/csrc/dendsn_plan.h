@@ -15,11 +15,12 @@ constexpr int kThreads = 256;  // 4 wave64s per block
 constexpr bool long_stash(int BL, int L, int KC, bool cm) { return BL * KC <= 4 && (L <= 4 || (KC == 1 && !cm)); }
 
 // The backward translation units are compiled once per surrogate derivative
-// (-DDENDSN_SG=0: atan, 1: sigmoid), which is bit 5 of the kernel variant V; their
-// launchers carry the suffix _sg0 / _sg1.
-#define DENDSN_SG_CAT2(name, k) name##_sg##k
-#define DENDSN_SG_CAT(name, k) DENDSN_SG_CAT2(name, k)
-#define DENDSN_SG_NAME(name) DENDSN_SG_CAT(name, DENDSN_SG)
+// (-DDENDSN_SG=0: atan, 1: sigmoid), which is bit 5 of the kernel variant V, and per
+// dendrite (-DDENDSN_SL=0: stateful, 1: Stateless); their launchers carry suffixes
+// like _sg0_sl1.  The first backward of a process loads one unit's kernels.
+#define DENDSN_SG_CAT2(name, k, m) name##_sg##k##_sl##m
+#define DENDSN_SG_CAT(name, k, m) DENDSN_SG_CAT2(name, k, m)
+#define DENDSN_SG_NAME(name) DENDSN_SG_CAT(name, DENDSN_SG, DENDSN_SL)
 
 // How the positions m = c * S + s of one sample are cut into per-block tiles.
 // Tiles never straddle a channel unless they hold whole channels, so a block's
@@ -129,6 +130,12 @@ constexpr int kNarrowSlots = 16;  // up to this many partial slots: one thread p
 // passes it to the launchers, to the template variant bits (bits 0, 1, 6).
 constexpr int variant_bits(int v) { return (v & 3) | ((v & 4) << 4); }
 #define DENDSN_EACH_VARIANT(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7)
+// those of one backward unit
+#if defined(DENDSN_SL) && DENDSN_SL
+#define DENDSN_EACH_UNIT_VARIANT(X) X(4) X(5) X(6) X(7)
+#else
+#define DENDSN_EACH_UNIT_VARIANT(X) X(0) X(1) X(2) X(3)
+#endif
 
 // Compiled (BL, L) mappings with one compartment per branch.  "Fast" mappings
 // move 8 or 16 bytes per lane; "generic" ones cover other branch counts.  For
@@ -148,10 +155,9 @@ constexpr int variant_bits(int v) { return (v & 3) | ((v & 4) << 4); }
 #define DENDSN_FAST_BF16_BWD(X) X(4, 1) X(8, 1) X(8, 16) X(4, 2) X(4, 4) X(4, 8) X(4, 16)
 #define DENDSN_GENERIC(X) X(1, 1) X(2, 1) X(3, 1) X(5, 1) X(6, 1) X(7, 1) X(5, 2) X(6, 2) X(7, 2)
 
-// Compiled (BL, L, KC) mappings with KC = 2 or 4 compartments per branch (stash
-// capacity 4).  Fast ones put 16 bytes of compartments in a lane (BL KC = 4
-// for fp32, 8 for bf16); generic ones hold a whole neuron of up to 14
-// compartments in one lane.
+// Compiled (BL, L, KC) mappings with KC = 2 or 4 compartments per branch.  Fast ones
+// put 16 bytes of compartments in a lane (BL KC = 4 for fp32, 8 for bf16); generic
+// ones hold a whole neuron of up to 14 compartments in one lane.
 #define DENDSN_KC_FAST_F32(X) X(2, 1, 2) X(2, 2, 2) X(2, 4, 2) X(2, 8, 2) X(2, 16, 2) \
                               X(1, 1, 4) X(1, 2, 4) X(1, 4, 4) X(1, 8, 4) X(1, 16, 4)
 #define DENDSN_KC_FAST_BF16(X) X(4, 1, 2) X(4, 2, 2) X(4, 4, 2) X(4, 8, 2) X(4, 16, 2) \
@@ -159,9 +165,8 @@ constexpr int variant_bits(int v) { return (v & 3) | ((v & 4) << 4); }
 #define DENDSN_KC_GENERIC(X) X(1, 1, 2) X(2, 1, 2) X(3, 1, 2) X(5, 1, 2) X(6, 1, 2) X(7, 1, 2) \
                              X(1, 1, 4) X(2, 1, 4) X(3, 1, 4)
 
-// Compiled (BL, L, KC) for the channel-major layout (stash capacity 4): the
-// fewest lanes per neuron that leave at most 4 compartments in a lane with
-// whole branches in each.
+// Compiled (BL, L, KC) for the channel-major layout: the fewest lanes per neuron that
+// leave at most 4 compartments in a lane with whole branches in each.
 #define DENDSN_CM(X) X(1, 1, 1) X(2, 1, 1) X(3, 1, 1) X(4, 1, 1) X(5, 1, 1) X(7, 1, 1) X(3, 2, 1) \
                      X(4, 2, 1) X(4, 4, 1) X(1, 1, 2) X(2, 1, 2) X(3, 1, 2) X(2, 2, 2) X(2, 4, 2) \
                      X(1, 1, 4) X(1, 2, 4) X(1, 4, 4)
