@@ -98,27 +98,6 @@ template <bool kCached, typename T>
 __device__ __forceinline__ T stream_load(const T* p);
 
 template <int BL>
-__device__ __forceinline__ void load_vec(const float* __restrict__ p, float (&v)[BL]) {
-  constexpr bool wide = BL * 4 > 16;
-  if constexpr (BL % 4 == 0) {
-#pragma unroll
-    for (int i = 0; i < BL / 4; ++i) {
-      const f32x4_t q = stream_load<wide>(reinterpret_cast<const f32x4_t*>(p) + i);
-      v[4 * i] = q.x; v[4 * i + 1] = q.y; v[4 * i + 2] = q.z; v[4 * i + 3] = q.w;
-    }
-  } else if constexpr (BL % 2 == 0) {
-#pragma unroll
-    for (int i = 0; i < BL / 2; ++i) {
-      const f32x2_t q = stream_load<wide>(reinterpret_cast<const f32x2_t*>(p) + i);
-      v[2 * i] = q.x; v[2 * i + 1] = q.y;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < BL; ++i) v[i] = stream_load<wide>(p + i);
-  }
-}
-
-template <int BL>
 __device__ __forceinline__ void store_vec(float* __restrict__ p, const float (&v)[BL]) {
   if constexpr (BL % 4 == 0) {
 #pragma unroll
@@ -190,9 +169,10 @@ __device__ __forceinline__ const P* uniform_ptr(const P* p) {  // the same for a
   return reinterpret_cast<const P*>(hi << 32 | lo);
 }
 
+// A lane's BL adjacent floats (checkpointed states), cached as in bload_raw.
 template <int BL>
-__device__ __forceinline__ void bload_vec(rsrc_t r, uint32_t off, float (&v)[BL], const float*) {
-  constexpr int kAuxNT = BL * 4 > 16 ? 0 : dendsn::kAuxNT;  // (see load_vec)
+__device__ __forceinline__ void bload_vec(rsrc_t r, uint32_t off, float (&v)[BL]) {
+  constexpr int kAuxNT = BL * 4 > 16 ? 0 : dendsn::kAuxNT;
   if constexpr (BL % 4 == 0) {
 #pragma unroll
     for (int i = 0; i < BL / 4; ++i) {
@@ -209,38 +189,6 @@ __device__ __forceinline__ void bload_vec(rsrc_t r, uint32_t off, float (&v)[BL]
   } else {
 #pragma unroll
     for (int i = 0; i < BL; ++i) v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off + 4u * i, 0, kAuxNT));
-  }
-}
-
-template <int BL>
-__device__ __forceinline__ void bload_vec(rsrc_t r, uint32_t off, float (&v)[BL], const bf16_t*) {
-  constexpr int kAuxNT = BL * 2 > 16 ? 0 : dendsn::kAuxNT;  // (see load_vec)
-  if constexpr (BL % 8 == 0) {
-#pragma unroll
-    for (int i = 0; i < BL / 8; ++i) {
-      const u32x4_t q = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16u * i, 0, kAuxNT);
-      v[8 * i + 0] = bf16_lo(q.x); v[8 * i + 1] = bf16_hi(q.x);
-      v[8 * i + 2] = bf16_lo(q.y); v[8 * i + 3] = bf16_hi(q.y);
-      v[8 * i + 4] = bf16_lo(q.z); v[8 * i + 5] = bf16_hi(q.z);
-      v[8 * i + 6] = bf16_lo(q.w); v[8 * i + 7] = bf16_hi(q.w);
-    }
-  } else if constexpr (BL % 4 == 0) {
-#pragma unroll
-    for (int i = 0; i < BL / 4; ++i) {
-      const u32x2_t q = __builtin_amdgcn_raw_buffer_load_b64(r, off + 8u * i, 0, kAuxNT);
-      v[4 * i + 0] = bf16_lo(q.x); v[4 * i + 1] = bf16_hi(q.x);
-      v[4 * i + 2] = bf16_lo(q.y); v[4 * i + 3] = bf16_hi(q.y);
-    }
-  } else if constexpr (BL % 2 == 0) {
-#pragma unroll
-    for (int i = 0; i < BL / 2; ++i) {
-      const uint32_t q = __builtin_amdgcn_raw_buffer_load_b32(r, off + 4u * i, 0, kAuxNT);
-      v[2 * i] = bf16_lo(q); v[2 * i + 1] = bf16_hi(q);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < BL; ++i)
-      v[i] = bf16_lo(uint32_t(__builtin_amdgcn_raw_buffer_load_b16(r, off + 2u * i, 0, kAuxNT)));
   }
 }
 
@@ -290,12 +238,6 @@ __device__ __forceinline__ void bstore_vec(rsrc_t r, uint32_t off, const float (
   }
 }
 
-__device__ __forceinline__ float bload_one(rsrc_t r, uint32_t off, uint32_t soff, const float*) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, soff, kAuxNT));
-}
-__device__ __forceinline__ float bload_one(rsrc_t r, uint32_t off, uint32_t soff, const bf16_t*) {
-  return bf16_lo(uint32_t(__builtin_amdgcn_raw_buffer_load_b16(r, off, soff, kAuxNT)));
-}
 __device__ __forceinline__ void bstore_one(rsrc_t r, uint32_t off, uint32_t soff, float v, float*) {
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, soff, kAuxNT);
 }
@@ -303,22 +245,10 @@ __device__ __forceinline__ void bstore_one(rsrc_t r, uint32_t off, uint32_t soff
   __builtin_amdgcn_raw_buffer_store_b16(to_bf16(v), r, off, soff, kAuxNT);
 }
 
-// A lane's E compartments of X / grad_x in the row starting at `row`: adjacent
-// (a vector access at the lane offset) or, in the channel-major layout, es
-// bytes apart (one access each, the uniform i * es in the scalar offset; the
-// lanes of a wave hold adjacent positions, so each access is contiguous across
-// the wave).  Through a buffer resource: the backward's segment path.
-template <int E, bool CM, typename IO>
-__device__ __forceinline__ void load_x(const IO* row, uint32_t off, uint32_t es, float (&v)[E]) {
-  const rsrc_t r = make_rsrc(row);
-  if constexpr (CM) {
-#pragma unroll
-    for (int i = 0; i < E; ++i) v[i] = bload_one(r, off, uint32_t(i) * es, row);
-  } else {
-    bload_vec<E>(r, off, v, row);
-  }
-}
-
+// A lane's E compartments of grad_x in the row starting at `row`: adjacent (a
+// vector access at the lane offset) or, in the channel-major layout, es bytes apart
+// (one access each, the uniform i * es in the scalar offset; the lanes of a wave
+// hold adjacent positions, so each access is contiguous across the wave).
 template <int E, bool CM, typename IO>
 __device__ __forceinline__ void store_gx(IO* row, uint32_t off, uint32_t es, const float (&v)[E]) {
   const rsrc_t r = make_rsrc(row);
@@ -356,11 +286,6 @@ __device__ __forceinline__ void store_gx_staged(IO* row, uint32_t span, const fl
       __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4_t*>(stage + d), r, span + d * 4, 0, kAuxNT);
   }
   __builtin_amdgcn_wave_barrier();
-}
-
-template <typename IO>
-__device__ __forceinline__ float load_row_one(const IO* row, uint32_t off) {
-  return bload_one(make_rsrc(row), off, 0, row);
 }
 
 // ---------------------------------------------------------------------------
@@ -1669,7 +1594,7 @@ __device__ __forceinline__ void load_visit(const BwdArgs& ba, const LaneOff& lo,
   const int64_t at_ck = ck ? int64_t(c.seg - 1) * a.N + c.n0 : 0;
   const uint32_t nb = uniform_u32(ck ? 0xFFFFFFFFu : 0u);
   if constexpr (!kSL<V>)
-    bload_vec<E>(make_rsrc(uniform_ptr(ba.ckpt + at_ck * a.P), nb), lo.c, r.v0, static_cast<const float*>(nullptr));
+    bload_vec<E>(make_rsrc(uniform_ptr(ba.ckpt + at_ck * a.P), nb), lo.c, r.v0);
   r.h0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(uniform_ptr(ba.ckh + at_ck), nb), lo.v, 0, kAuxNT));
   const int64_t row = int64_t(c.c0) * a.N;
   load_chunk_raw<IO, E, KS, kCM<V>, GV, ST, true>(a, lo, static_cast<const IO*>(a.x) + c.nx0 + row * a.P,
