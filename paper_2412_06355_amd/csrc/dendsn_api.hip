@@ -259,6 +259,21 @@ dendsn_status check_cfg(const dendsn_cfg* c) {
   return DENDSN_OK;
 }
 
+// One group's parameter-gradient partials, a word each (the array of the channels'
+// sums is rounded up to 256 bytes in the workspace).
+int64_t group_bytes(const dendsn_cfg* c, const Plan& p) {
+  return (int64_t(p.tpc) * c->C * (2 * c->B + c->B * c->comps_per_branch) + 2 * p.ntiles) * int64_t(sizeof(float));
+}
+
+// Eight bf16 branches over two lanes (longer sequences in the backward) need twice
+// the tiles, and so twice the partials, of one lane.  Where that alone would take a
+// layer beyond the fixed scratch (more than 2^18 tiles), one lane keeps them.
+bool two_lanes_fit(const dendsn_cfg* c) {
+  if (c->B != 8 || c->comps_per_branch != 1 || c->io != DENDSN_IO_BF16 || c->S < kThreads / 2) return true;
+  const int64_t tiles = c->C * ceil_div(c->S, kThreads / 2);
+  return tiles * (3 * 8 + 2) * int64_t(sizeof(float)) + 256 <= int64_t(DENDSN_NOALLOC_SCRATCH_BYTES);
+}
+
 // Tiling and batch grouping.  The two directions may split a neuron over lanes
 // differently only where the branch sum's tree stays the same (powers of two),
 // so the backward's recompute adds the branch terms as the forward did.
@@ -275,7 +290,7 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
     // 523 -> 408 us with one lane and two positions per lane)
     if (!bwd && is_pow2(p.BL) && p.L >= 2 && p.BL * p.KC <= 4) { p.BL *= 2; p.L /= 2; }
   } else {
-    choose_mapping(c->B, c->comps_per_branch, c->io, bwd, Ke > 4, &p.BL, &p.L, &p.fast);
+    choose_mapping(c->B, c->comps_per_branch, c->io, bwd, Ke > 4 && two_lanes_fit(c), &p.BL, &p.L, &p.fast);
   }
   const int L = p.L;
   const int esz = c->io == DENDSN_IO_BF16 ? 2 : 4;
@@ -406,12 +421,14 @@ Plan make_plan(const dendsn_cfg* c, bool bwd) {
   // lane's fp32 chain nor the number of fp32 roundings between a lane and the output
   // grows with the group.  With several positions per lane fewer groups gained and lost
   // (32x32, 64 channels, 16 samples: 34.3 us with 16 groups, 36.4 with 4): unchanged.
-  // The float64 sums have to fit beside what else a block keeps in LDS.
+  // The float64 sums have to fit beside what else a block keeps in LDS, and the
+  // partials' two words each must not outgrow the fixed scratch where the groups above fit.
   const int64_t fold_bytes = int64_t(2 * p.BL + E + 2) * kThreads * 8;
   if (bwd && p.mode == kSpatial && p.nw == 1 && !wide_sf && c->batch_groups == 0 && fold_bytes <= kFoldBytes) {
-    const int64_t items = std::min(std::min<int64_t>(4, 24 / c->T), c->batch * p.ntiles / 512);
-    if (items > ceil_div(c->batch, G)) {
-      G = ceil_div(c->batch, items);
+    const int64_t items = std::min(std::min(std::min<int64_t>(4, 24 / c->T), c->batch), c->batch * p.ntiles / 512);
+    const int64_t fewer = items > 0 ? ceil_div(c->batch, items) : G;
+    if (items > ceil_div(c->batch, G) && (2 * fewer <= G || 2 * fewer * group_bytes(c, p) + 256 <= int64_t(DENDSN_NOALLOC_SCRATCH_BYTES))) {
+      G = fewer;
       p.fold = 1;
     }
   }

@@ -2136,9 +2136,12 @@ hipError_t launch_bwd(const Plan& pl, const BwdArgs& ba, hipStream_t stream) {
       if (fast) DENDSN_BWD(kSegments, true)
       DENDSN_BWD(kSegments, false)
     }
-  // (eight bf16 branches run longer segments over two lanes)
-  if constexpr (KS == 8 || !(long_stash(BL, L, kKC<V>, kCM<V>) || (BL == 8 && L == 1 && kKC<V> == 1))) {
-    if (fast) DENDSN_BWD(kVisits, true)
+  // (eight bf16 branches run longer segments over two lanes, unless those have too
+  // many tiles for the fixed scratch: rare, so one kernel with and without gates)
+  constexpr bool kRare = BL == 8 && L == 1 && kKC<V> == 1;
+  if constexpr (KS == 8 || !long_stash(BL, L, kKC<V>, kCM<V>)) {
+    if constexpr (!kRare)
+      if (fast) DENDSN_BWD(kVisits, true)
     DENDSN_BWD(kVisits, false)
   }
   return hipErrorInvalidValue;  // (the plan gives segments above 4 steps a mapping and stash compiled for them)

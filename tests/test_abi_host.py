@@ -324,3 +324,19 @@ def test_noalloc_backward_argument_checks(lib):
     # the binding's size is the header's
     m = re.search(r"#define DENDSN_NOALLOC_SCRATCH_BYTES \(\(size_t\)(\d+) << (\d+)\)", open(HEADER).read())
     assert m and int(m.group(1)) << int(m.group(2)) == dendsn.NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("lanes,kw", [
+    (4, dict(T=2, batch=3, C=5896, S=1331, B=16)),      # one group: nothing to sum apart
+    (2, dict(T=5, batch=1, C=7945, S=2196, B=12)),
+    (1, dict(T=8, batch=17, C=16136, S=4037, B=8)),     # two lanes a neuron: twice the tiles
+    (1, dict(T=33, batch=40, C=161500, S=129, B=8, ckpt_every=8)),
+])
+def test_layers_of_many_tiles_stay_within_the_scratch(lib, lanes, kw):
+    """Layers of so many tiles that one word a partial, one group and the fewest lanes
+    a neuron just fit the fixed scratch array: neither the second word of items that are
+    summed apart nor more lanes a neuron may take them beyond it."""
+    c = dendsn.DendSNConfig(io="bf16", stateful=True, **kw)
+    tiles = c.C * -(-c.S * lanes // 256)
+    assert tiles * (3 * c.B + 2) * 4 <= dendsn.NOALLOC_SCRATCH_BYTES
+    assert dendsn.dendsn_bwd_workspace_bytes(c) <= dendsn.NOALLOC_SCRATCH_BYTES

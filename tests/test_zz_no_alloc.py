@@ -69,6 +69,40 @@ def test_noalloc_backward_equals_workspace_backward(gpu_device):
         _assert_identical(ref, out)
 
 
+@pytest.mark.parametrize("T,K", [(5, 0), (16, 8)])
+def test_one_lane_where_two_would_outgrow_the_scratch(gpu_device, T, K):
+    """Eight bf16 branches, more than four steps, so many tiles that two lanes a neuron
+    would need more than the scratch array: the layer runs one lane a neuron, and the
+    channels' gradients are those of a layer of few channels (two lanes)."""
+    import torch
+
+    few, reps = _cfg(T=T, batch=1, C=512, S=129, B=8, io="bf16", ckpt_every=K), 320
+    many = few.with_(C=few.C * reps)
+    case = make_case(few, seed=5, name=f"one lane T={T} K={K}", random_affine=True)
+    announce(f"noalloc one lane: {many}")
+    d = to_device(case, gpu_device)
+    want, _ = _both(case, gpu_device)
+    assert dendsn.dendsn_bwd_workspace_bytes(many) <= dendsn.NOALLOC_SCRATCH_BYTES
+    x, gs = d["x"].repeat(1, reps, 1), d["gS"].repeat(1, reps)
+    kappa, xi, zeta = (d[k].repeat(reps, 1) for k in ("kappa", "xi", "zeta"))
+    _, _, ckpt = dendsn.forward(many, x, d["alpha"], kappa, xi, zeta, None)
+    out = {k: torch.full_like(v.repeat(reps, 1) if v.dim() == 2 else v, float("nan"))
+           for k, v in want.items() if k != "grad_x"}
+    out["grad_x"] = torch.full_like(x, float("nan"))
+    dendsn.dendsn_backward_noalloc(many, x, d["alpha"], None, kappa, xi, zeta, None, ckpt, gs, None, out["grad_x"],
+                                   out["grad_alpha"], out["grad_beta"], out["grad_kappa"], out["grad_xi"],
+                                   out["grad_zeta"])
+    torch.cuda.synchronize(gpu_device)
+    assert torch.equal(_bits(out["grad_x"]), _bits(want["grad_x"].repeat(1, reps, 1)))
+    for k in ("grad_kappa", "grad_xi", "grad_zeta"):
+        got = out[k].view(reps, few.C, -1)
+        # a channel's T x 129 terms, in another order: a lane's T in a row and eight
+        # levels of additions each way
+        tol = 2 * (T + 8) * 2.0 ** -24 * (T * 129) ** 0.5 * want[k].abs().max()
+        assert (got - want[k]).abs().max() <= tol, k
+        assert torch.equal(got, got[:1].expand_as(got)), k
+
+
 def test_noalloc_twice_on_a_shrinking_layer(gpu_device):
     """Two calls in a row, the second on a smaller layer of the same tiling."""
     for name, batch in (("first", 6), ("second-smaller", 2)):
