@@ -1902,7 +1902,8 @@ __device__ __forceinline__ void reduce_folded(const BwdArgs& ba, const Pos& pos)
 #pragma unroll
     for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off);
     if (r == 0) {
-      const float hi = float(s), lo = float(s - double(hi));
+      const float hi = float(s);
+      const float lo = __builtin_isinf(hi) ? 0.0f : float(s - double(hi));  // (an overflowed sum stays infinite)
       if (o < W) {
         const int64_t p = 2 * (int64_t(pos.g) * a.tpc + pos.tile % a.tpc);
         ba.wsP[partial_index(ba, pos.c, o, p)] = hi;

@@ -764,6 +764,37 @@ def test_items_of_a_group_are_summed_apart(gpu_device, shape, variant):
         assert (a[name] - b[name]).abs().max() <= tol, name
 
 
+@pytest.mark.parametrize("shape", [FOLDED[0], FOLDED[5]], ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}-K{}".format(*s))
+def test_overflowing_sums_of_folded_items_are_infinite(gpu_device, shape):
+    """A block's sum beyond float32's range is infinite, as it is in one-item groups; the
+    second word of its partial (what rounding left over) must not turn it into NaN."""
+    import torch
+
+    T, batch, C, S, B, k, io, layout, K = shape
+    c = cfg(T=T, batch=batch, C=C, S=S, B=B, comps_per_branch=k, io=io, layout=layout, ckpt_every=K, beta=0.6,
+            psi="identity", detach_reset=True)
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(17)
+    dt = torch.bfloat16 if io == "bf16" else torch.float32
+    announce(f"folded overflow/{shape}")
+    # positive drive, coefficients and spike gradients: a channel's terms have one sign
+    # (xi away from 0: 1 / norm, on the way to grad_x, stays below 5)
+    x = torch.rand((T, c.N, c.P), device=gpu_device, generator=g).to(dt)
+    gs = (1e37 * (0.5 + torch.rand((T, c.N), device=gpu_device, generator=g))).to(dt)
+    alpha = torch.full((1,), 0.6, device=gpu_device)
+    kappa = 0.2 + 0.2 * torch.rand((C, B), device=gpu_device, generator=g)
+    xi = -0.2 - 0.2 * torch.rand((C, B * k), device=gpu_device, generator=g)
+    _, _, ckpt = dendsn.forward(c, x, alpha, kappa, xi, None, None)
+    a = dendsn.backward(c, x, alpha, kappa, xi, None, None, ckpt, gs)
+    b = dendsn.backward(c.with_(batch_groups=batch), x, alpha, kappa, xi, None, None, ckpt, gs)
+    assert torch.isfinite(a["grad_x"]).all()
+    for name in ("grad_kappa", "grad_xi"):
+        assert torch.isinf(b[name]).all(), name
+    for name in ("grad_kappa", "grad_xi", "grad_zeta", "grad_alpha", "grad_beta"):
+        inf = torch.isinf(b[name])
+        assert not a[name].isnan().any() and torch.equal(a[name][inf], b[name][inf]), name
+
+
 def test_forward_without_checkpoints_for_inference(gpu_device):
     import torch
 
