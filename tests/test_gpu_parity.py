@@ -705,12 +705,13 @@ def test_small_layers_tiles_and_groups(gpu_device, shape, variant):
 
 
 # --- backward groups of several items whose sums are folded in float64: every lane
-# count and pipeline (T, batch, C, S, B, k, io, layout, K) ---
+# count and pipeline (T, batch, C, S, B, k, io, layout, K).  A group takes 24 / T items,
+# up to four: no more than twelve steps, or each item is a group of its own ---
 FOLDED = [
     (6, 64, 16, 256, 2, 2, "f32", "npb", 0),
     (4, 128, 16, 256, 2, 2, "bf16", "channel_major", 0),
-    (33, 64, 16, 256, 4, 1, "bf16", "npb", 0),        # chunk starts and folded sums in LDS
-    (16, 64, 16, 256, 4, 1, "f32", "npb", 4),         # segments
+    (12, 64, 16, 256, 5, 1, "bf16", "npb", 0),        # chunk starts and folded sums in LDS
+    (12, 64, 16, 256, 4, 1, "f32", "npb", 4),         # segments
     (10, 64, 16, 256, 2, 2, "f32", "channel_major", 0),
     (3, 64, 16, 300, 5, 2, "bf16", "npb", 0),         # wide rows, two tiles a channel
     (6, 128, 8, 129, 2, 2, "f32", "npb", 0),          # one map a tile, idle lanes
@@ -764,7 +765,7 @@ def test_items_of_a_group_are_summed_apart(gpu_device, shape, variant):
         assert (a[name] - b[name]).abs().max() <= tol, name
 
 
-@pytest.mark.parametrize("shape", [FOLDED[0], FOLDED[5]], ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}-K{}".format(*s))
+@pytest.mark.parametrize("shape", [FOLDED[0], FOLDED[2], FOLDED[5]], ids=lambda s: "T{}b{}C{}S{}B{}k{}{}-{}-K{}".format(*s))
 def test_overflowing_sums_of_folded_items_are_infinite(gpu_device, shape):
     """A block's sum beyond float32's range is infinite, as it is in one-item groups; the
     second word of its partial (what rounding left over) must not turn it into NaN."""
